@@ -109,8 +109,6 @@ struct Job {
     uint64_t *woff;      // encoder: payload word offset of each chunk
     uint64_t *zoff;      // encoder: first outlier slot of each chunk
     uint2 *mm_part;      // per-unit (min, max) key partials: minmax units (REL) or tiles (ABS)
-    float *crec;         // per full tile: values of its even-point grid after the coarse levels
-    uint8_t *ccode;      // per full tile: codes of its owned even points (compression)
     uint64_t dims[3];
     uint64_t N;
     uint32_t nb[3];      // blocks per axis = ceil(d / 16)
@@ -129,9 +127,6 @@ struct Job {
     uint64_t mm_begin, tune_begin, tile_begin, chunk_begin, group_begin, dblk_begin, out_begin;
     uint64_t n_mm, n_tune, n_tiles, n_groups, n_dblk;
     uint32_t n_full[3];  // full 17^3 blocks per axis (tuner sample)
-    uint32_t nf[3];      // full tiles per axis: coarse slot of tile (bx, by, bz0/TZ) is
-                         // (bx * nf[1] + by) * nf[2] + bz0/TZ
-    uint32_t pad3;
     uint32_t n_samples;  // tuner sample size
     // decompression: section layout and bound parsed from the header
     uint64_t off_oidx, off_oval, off_payload, n_out, payload_words;
@@ -162,8 +157,10 @@ struct JobList {
     uint64_t total; // total units of the launch's work kind
 };
 
-// Tile depths along z: 1, 2 or 4 blocks (index 0, 1, 2).
-constexpr int kTileDepths = 3;
+// Tile kinds: 1, 2 or 4 blocks along z (kinds 0, 1, 2), and the flat tiles (4
+// blocks along z) of fields of a single x plane.
+constexpr int kTileKinds = 4, kFlatKind = 3;
+constexpr int kFlatDepth = 4;
 
 // Counters reset at the start of every call.
 struct Counters {
@@ -171,9 +168,6 @@ struct Counters {
     uint32_t dec_next;
     uint32_t lc_next;      // bitwise-redundancy chunks
     uint32_t ou_next;      // outlier units
-    // per tile depth (1, 2, 4) and XCD: tiles claimed by predict / reconstruct
-    uint32_t tile_next[kTileDepths][8];
-    uint32_t pad[12];
 };
 
 // ---- kernel launchers (each defined next to its kernel) ----
@@ -187,11 +181,10 @@ void launch_eps(const Job *d_jobs, int njobs, hipStream_t s);
 void launch_tune(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s);
 void launch_tune_pick(const Job *d_jobs, int njobs, hipStream_t s);
 // The tile kernels run over the tiles [lo, hi) of the work list, which belong
-// to the njobs jobs at d_jobs (all of tile depth tile_z); ctr: their eight
-// claim counters.
-void launch_predict(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int tile_z, int grid,
-                    uint32_t *ctr, hipStream_t s);
-int predict_blocks_per_cu(int tile_z);
+// to the njobs jobs at d_jobs (all of one tile kind).
+void launch_predict(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int kind, int grid,
+                    hipStream_t s);
+int predict_blocks_per_cu(int kind);
 void launch_codebook(const Job *d_jobs, int njobs, hipStream_t s);
 void launch_encode(const Job *d_jobs, int njobs, uint64_t total_chunks, uint64_t total_groups,
                    Counters *cnt, int grid, hipStream_t s);
@@ -210,18 +203,11 @@ constexpr int kDecSub = 256;
 __host__ __device__ inline uint64_t dec_subblocks(uint64_t chunks) { return 2 * cdiv(chunks, 2 * kDecSub); }
 void launch_decode(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, int cus, hipStream_t s);
 void launch_scatter(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s);
-void launch_reconstruct(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int tile_z,
-                        int grid, uint32_t *ctr, hipStream_t s);
-// Levels of stride 8, 4, 2 of every full tile on its grid of even points
-// (one wave per tile), ahead of k_predict / k_reconstruct.
-void launch_coarse(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int tile_z,
-                   bool compress, hipStream_t s);
-// Values (4 bytes each) and codes of one tile's even-point grid.
-uint64_t coarse_values_per_tile(int tile_z);
-uint64_t coarse_codes_per_tile(int tile_z);
+void launch_reconstruct(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int kind, int grid,
+                        hipStream_t s);
 // Workspace bound over every shape of n points (a stream's field size before
 // its header is read): hiz_workspace_bound of an n x 1 x 1 field plus the
-// most pre-pass slots any shape of n points can have.
+// largest tile allowance any shape of n points can have.
 uint64_t workspace_bound_points(uint64_t n);
 // Serving helpers (runtime.hip): pinned staging reserved for batches of up to
 // n fields; decompression submit with each stream's first kOffChunks bytes
@@ -231,7 +217,7 @@ hiz_status ctx_decompress_submit_hdrs(hiz_ctx *c, int n, const void *const *d_in
                                       const uint64_t *in_sizes, float *const *d_fields,
                                       const uint64_t *field_caps, hipStream_t s,
                                       const uint8_t *h_hdrs);
-int reconstruct_blocks_per_cu(int tile_z);
+int reconstruct_blocks_per_cu(int kind);
 // Bitwise-redundancy stages, reordering and outliers (k_lc.hip).
 void launch_reorder(const Job *d_jobs, int njobs, uint64_t max_n, bool inverse, hipStream_t s);
 void launch_outliers(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, hipStream_t s);
@@ -254,15 +240,6 @@ template <class T> __device__ __forceinline__ HIZ_GLOBAL T *gmem(T *p)
 typedef float hiz_f4v __attribute__((ext_vector_type(4)));
 typedef uint32_t hiz_u4v __attribute__((ext_vector_type(4)));
 typedef uint32_t hiz_u2v __attribute__((ext_vector_type(2)));
-// Global memory straight into LDS, no registers in between: every lane of
-// the wave names its own 4-byte source, and the wave's 64 words land in order
-// at dst[0..63] (dst is the same for the whole wave). The loads count as
-// vector-memory loads: lds_fill_wait() retires them before a barrier makes
-// the words visible to the workgroup.
-__device__ __forceinline__ void lds_load_word(HIZ_GLOBAL const float *src, float *dst)
-{
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
-}
 // Workgroup barrier for data exchanged through LDS only: LDS operations
 // retire first, global loads and stores stay in flight across it (a
 // __syncthreads() would also wait for every outstanding global access, such
@@ -271,7 +248,6 @@ __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
-__device__ __forceinline__ void lds_fill_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ float4 gload_f4(HIZ_GLOBAL const float *p)
 {
     const hiz_f4v v = *(HIZ_GLOBAL const hiz_f4v *)p;

@@ -45,7 +45,7 @@ struct Pending {
 struct GraphKey {
     int kind; // 0 compress, 1 decompress
     int njobs;
-    uint64_t v[24];
+    uint64_t v[12 + 4 * kTileKinds];
     const void *ws;
     const void *pinned;
 };
@@ -88,8 +88,8 @@ struct hiz_ctx {
     std::vector<Pending> pending;
     std::vector<hipEvent_t> events;
     size_t next_event = 0;
-    int pred_bpc[5] = {0, 0, 0, 0, 0};
-    int rec_bpc[5] = {0, 0, 0, 0, 0};
+    int pred_bpc[kTileKinds] = {0, 0, 0, 0};
+    int rec_bpc[kTileKinds] = {0, 0, 0, 0};
     int enc_bpc = 0;
     bool graphs = false;
     hipStream_t cap_stream = nullptr;
@@ -195,7 +195,11 @@ LaunchDefaults default_launch(const uint64_t dims[3])
     return L;
 }
 
-int depth_index(int tz) { return tz == 1 ? 0 : tz == 2 ? 1 : 2; }
+// Tile kind of a field: by its tile depth, or flat when it has one x plane.
+int tile_kind(const Job &J)
+{
+    return J.dims[0] == 1 ? kFlatKind : J.tz == 1 ? 0 : J.tz == 2 ? 1 : 2;
+}
 
 // ---- profiling ----
 hipEvent_t take_event(hiz_ctx *c)
@@ -341,16 +345,16 @@ bool debug_on()
     return v == 1;
 }
 
-int predict_grid(hiz_ctx *c, int tz, uint64_t total, bool rec)
+int predict_grid(hiz_ctx *c, int kind, uint64_t total, bool rec)
 {
     int *cache = rec ? c->rec_bpc : c->pred_bpc;
-    if (!cache[tz]) {
-        cache[tz] = rec ? reconstruct_blocks_per_cu(tz) : predict_blocks_per_cu(tz);
+    if (!cache[kind]) {
+        cache[kind] = rec ? reconstruct_blocks_per_cu(kind) : predict_blocks_per_cu(kind);
         if (debug_on())
-            fprintf(stderr, "[hiz] %s tile_z=%d: %d CUs x %d workgroups per CU\n",
-                    rec ? "reconstruct" : "predict", tz, c->cus, cache[tz]);
+            fprintf(stderr, "[hiz] %s tile kind %d: %d CUs x %d workgroups per CU\n",
+                    rec ? "reconstruct" : "predict", kind, c->cus, cache[kind]);
     }
-    uint64_t g = (uint64_t)c->cus * cache[tz];
+    uint64_t g = (uint64_t)c->cus * cache[kind];
     if (g >= 8)
         g &= ~uint64_t(7);
     if (total < g)
@@ -568,17 +572,17 @@ hiz_status resolve_params(hiz_ctx *c, const hiz_params *params, hiz_params &p, i
     return rc ? fail(c, rc, "%s", msg) : HIZ_OK;
 }
 
-// Tiles whose owned points all lie inside the field (their coarse levels run
-// in the pre-pass), per axis: a block starting at 16b qualifies when
-// 16b + 16 <= d.
-void set_full_tiles(Job &J, int tz)
+// Per tile of 16 x 16 x 16 tz points, the workspace allowance that
+// hiz_workspace_bound and the limit of the allocation-free call are documented
+// with: 9 x 9 x (8 tz + 1) values and 8 x 8 x 8 tz codes. The layout itself
+// takes none of it (all levels of a tile run in LDS); the published sizes and
+// the limit stay as callers know them.
+uint64_t tile_allowance(uint64_t tz) { return 4 * 81 * (8 * tz + 1) + 512 * tz; }
+uint64_t tile_allowance(const Job &J)
 {
-    J.nf[0] = (uint32_t)(J.dims[0] / kAnchor);
-    J.nf[1] = (uint32_t)(J.dims[1] / kAnchor);
-    J.nf[2] = (uint32_t)(J.dims[2] / kAnchor / (uint64_t)tz);
+    return (J.dims[0] / kAnchor) * (J.dims[1] / kAnchor) * (J.dims[2] / kAnchor / J.tz) *
+           tile_allowance(J.tz);
 }
-
-uint64_t full_tiles(const Job &J) { return (uint64_t)J.nf[0] * J.nf[1] * J.nf[2]; }
 
 // Geometry and parameters of one field to compress; device pointers are
 // filled in by the caller once the workspace is laid out.
@@ -614,6 +618,8 @@ hiz_status plan_compress(const float *d_field, const uint64_t dims[3], int mode,
     const uint32_t chunk = p.chunk ? p.chunk : dl.chunk;
     if (!tz)
         tz = dl.tz;
+    if (dims[0] == 1)
+        tz = kFlatDepth;
     memset(&J, 0, sizeof(J));
     J.field = d_field;
     J.stream = static_cast<uint8_t *>(d_out);
@@ -653,7 +659,6 @@ hiz_status plan_compress(const float *d_field, const uint64_t dims[3], int mode,
     J.n_tune = (uint64_t)J.n_samples * 9;
     J.n_tiles = (uint64_t)J.nb[0] * J.nb[1] * J.ntz;
     J.n_groups = cdiv(J.n_chunks, kEncGroupChunks);
-    set_full_tiles(J, tz);
     J.pipe = (uint8_t)p.pipeline;
     J.reorder = (uint8_t)(p.reorder ? 1 : 0);
     if (J.pipe == PIPE_TP) {
@@ -689,6 +694,8 @@ void plan_decompress(const Parsed &P, const void *d_in, uint64_t in_size, float 
         J.nb[k] = (uint32_t)cdiv(J.dims[k], kAnchor);
     }
     J.N = P.N;
+    if (J.dims[0] == 1)
+        tz = kFlatDepth;
     J.tz = (uint8_t)tz;
     J.ntz = (uint32_t)cdiv(J.nb[2], tz);
     J.n_anchors = (uint64_t)J.nb[0] * J.nb[1] * J.nb[2];
@@ -702,7 +709,6 @@ void plan_decompress(const Parsed &P, const void *d_in, uint64_t in_size, float 
     J.idx_bytes = (uint8_t)P.idx_bytes;
     J.n_tiles = (uint64_t)J.nb[0] * J.nb[1] * J.ntz;
     J.n_dblk = dec_subblocks(J.n_chunks);
-    set_full_tiles(J, tz);
     J.off_oidx = P.off_oidx;
     J.off_oval = P.off_oval;
     J.off_payload = P.off_payload;
@@ -727,9 +733,9 @@ struct Totals {
     uint64_t max_n = 0;        // largest field (reordering launch)
     bool reorder = false;      // some field's codes are reordered
     uint64_t max_clear = 0;    // longest look-back array any field clears at the start
-    // per tile depth (jobs ordered by depth): jobs [jlo, jhi) with tiles [tlo, thi)
-    int jlo[kTileDepths] = {0, 0, 0}, jhi[kTileDepths] = {0, 0, 0};
-    uint64_t tlo[kTileDepths] = {0, 0, 0}, thi[kTileDepths] = {0, 0, 0};
+    // per tile kind (jobs ordered by kind): jobs [jlo, jhi) with tiles [tlo, thi)
+    int jlo[kTileKinds] = {0, 0, 0, 0}, jhi[kTileKinds] = {0, 0, 0, 0};
+    uint64_t tlo[kTileKinds] = {0, 0, 0, 0}, thi[kTileKinds] = {0, 0, 0, 0};
 };
 
 // Lay out the workspace for `jobs`, set their prefixes and device pointers,
@@ -745,14 +751,13 @@ struct Layout {
 
 // Workspace sections of one field (offsets from the workspace base).
 struct Sections {
-    uint64_t st, codes, crec, ccode, dt, lba, lbb, woff, zoff, mm, seq, hpay, lbc, lbd;
+    uint64_t st, codes, dt, lba, lbb, woff, zoff, mm, seq, hpay, lbc, lbd;
 };
 
 // Take one field's sections from the arena and add its work units to the
 // launch totals (its work-list prefixes are the totals before it).
 void take_sections(Arena &A, Job &J, bool decompress, Totals &T, Sections &o)
 {
-    const int tz = J.tz;
     memset(&o, 0, sizeof(o));
     o.st = A.take(sizeof(FieldState));
     o.codes = A.take(J.N);
@@ -769,8 +774,6 @@ void take_sections(Arena &A, Job &J, bool decompress, Totals &T, Sections &o)
     T.max_n = std::max(T.max_n, J.N);
     T.reorder = T.reorder || J.reorder;
     T.max_clear = std::max(T.max_clear, std::max(J.n_lc, J.n_ou));
-    o.crec = A.take(4 * coarse_values_per_tile(tz) * full_tiles(J));
-    o.ccode = decompress ? 0 : A.take(coarse_codes_per_tile(tz) * full_tiles(J));
     if (decompress) {
         o.dt = A.take(sizeof(DecTables));
         o.lba = A.take(8 * J.n_dblk);
@@ -810,8 +813,6 @@ void bind_sections(uint8_t *ws, Job &J, bool decompress, const Sections &o)
     J.hpay = J.pipe == PIPE_CR ? ws + o.hpay : nullptr;
     J.lb_c = reinterpret_cast<uint64_t *>(ws + o.lbc);
     J.lb_d = reinterpret_cast<uint64_t *>(ws + o.lbd);
-    J.crec = reinterpret_cast<float *>(ws + o.crec);
-    J.ccode = decompress ? nullptr : ws + o.ccode;
     J.lb_a = reinterpret_cast<uint64_t *>(ws + o.lba);
     if (decompress) {
         J.dt = reinterpret_cast<DecTables *>(ws + o.dt);
@@ -829,35 +830,31 @@ bool totals_fit(const Totals &T)
            T.tiles <= 0xffffffffull && T.lc <= 0xffffffffull && T.ou <= 0xffffffffull;
 }
 
-// Per-depth job and tile ranges of a Job table ordered by tile depth.
-void depth_ranges(const Job *jobs, int nj, Totals &T)
+// Per-kind job and tile ranges of a Job table ordered by tile kind.
+void kind_ranges(const Job *jobs, int nj, Totals &T)
 {
-    for (int d = 0; d < kTileDepths; d++) {
-        T.jlo[d] = T.jhi[d] = 0;
-        T.tlo[d] = T.thi[d] = 0;
-    }
     int j = 0;
-    for (int d = 0; d < kTileDepths; d++) {
-        T.jlo[d] = j;
-        T.tlo[d] = j < nj ? jobs[j].tile_begin : T.tiles;
-        while (j < nj && depth_index(jobs[j].tz) == d)
+    for (int k = 0; k < kTileKinds; k++) {
+        T.jlo[k] = j;
+        T.tlo[k] = j < nj ? jobs[j].tile_begin : T.tiles;
+        while (j < nj && tile_kind(jobs[j]) == k)
             j++;
-        T.jhi[d] = j;
-        T.thi[d] = j < nj ? jobs[j].tile_begin : T.tiles;
+        T.jhi[k] = j;
+        T.thi[k] = j < nj ? jobs[j].tile_begin : T.tiles;
     }
 }
 
-// Stable order of a call's jobs by tile depth, so that each depth's jobs and
-// tiles are contiguous (one launch of the tile kernels per depth); `field`
+// Stable order of a call's jobs by tile kind, so that each kind's jobs and
+// tiles are contiguous (one launch of the tile kernels per kind); `field`
 // and `extra` (when not empty) follow the jobs.
-void order_by_depth(std::vector<Job> &jobs, std::vector<int> &field, std::vector<uint64_t> &extra)
+void order_by_kind(std::vector<Job> &jobs, std::vector<int> &field, std::vector<uint64_t> &extra)
 {
     const size_t n = jobs.size();
     std::vector<size_t> idx(n);
     for (size_t i = 0; i < n; i++)
         idx[i] = i;
     std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
-        return depth_index(jobs[a].tz) < depth_index(jobs[b].tz);
+        return tile_kind(jobs[a]) < tile_kind(jobs[b]);
     });
     std::vector<Job> j2(n);
     std::vector<int> f2(n);
@@ -885,7 +882,7 @@ hiz_status layout(hiz_ctx *c, std::vector<Job> &jobs, bool decompress, Totals &T
     T = Totals();
     for (int j = 0; j < nj; j++)
         take_sections(A, jobs[j], decompress, T, o[j]);
-    depth_ranges(jobs.data(), nj, T);
+    kind_ranges(jobs.data(), nj, T);
     if (!totals_fit(T))
         return fail(c, HIZ_ERR_ARG, "batch too large for one launch");
     hiz_status rc = ensure_ws(c, A.off);
@@ -909,13 +906,6 @@ hiz_status layout(hiz_ctx *c, std::vector<Job> &jobs, bool decompress, Totals &T
 
 // The launch sequence of compression (Sec. 5: range and bound, tuner,
 // interpolation + quantization + histogram, codebook, encoding) for all jobs.
-// Claim counters of the tile kernels of one depth (a device address).
-uint32_t *depth_counters(const Layout &L, int d)
-{
-    return reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(L.d_cnt) +
-                                        offsetof(Counters, tile_next)) + 8 * d;
-}
-
 void enqueue_compress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipStream_t s,
                       bool prof)
 {
@@ -941,23 +931,13 @@ void enqueue_compress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipS
         Scope sc(c, s, "tune_pick", prof, true);
         launch_tune_pick(L.d_jobs, nj, s);
     }
-    // the tile kernels: one launch per tile depth present
-    for (int d = 0; d < kTileDepths; d++) {
-        if (T.thi[d] <= T.tlo[d])
+    // the tile kernels: one launch per tile kind present
+    for (int k = 0; k < kTileKinds; k++) {
+        if (T.thi[k] <= T.tlo[k])
             continue;
-        const int tz = 1 << d;
-        const Job *dj = L.d_jobs + T.jlo[d];
-        const int nd = T.jhi[d] - T.jlo[d];
-        {
-            Scope sc(c, s, "coarse", prof, true);
-            launch_coarse(dj, nd, T.tlo[d], T.thi[d], tz, true, s);
-        }
-        {
-            Scope sc(c, s, "predict_quant", prof, true);
-            launch_predict(dj, nd, T.tlo[d], T.thi[d], tz,
-                           predict_grid(c, tz, T.thi[d] - T.tlo[d], false), depth_counters(L, d),
-                           s);
-        }
+        Scope sc(c, s, "predict_quant", prof, true);
+        launch_predict(L.d_jobs + T.jlo[k], T.jhi[k] - T.jlo[k], T.tlo[k], T.thi[k], k,
+                       predict_grid(c, k, T.thi[k] - T.tlo[k], false), s);
     }
     if (T.reorder) {
         Scope sc(c, s, "reorder", prof, true);
@@ -1014,22 +994,12 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
         Scope sc(c, s, "scatter", prof, true);
         launch_scatter(L.d_jobs, nj, T.out, s);
     }
-    for (int d = 0; d < kTileDepths; d++) {
-        if (T.thi[d] <= T.tlo[d])
+    for (int k = 0; k < kTileKinds; k++) {
+        if (T.thi[k] <= T.tlo[k])
             continue;
-        const int tz = 1 << d;
-        const Job *dj = L.d_jobs + T.jlo[d];
-        const int nd = T.jhi[d] - T.jlo[d];
-        {
-            Scope sc(c, s, "coarse_rec", prof, true);
-            launch_coarse(dj, nd, T.tlo[d], T.thi[d], tz, false, s);
-        }
-        {
-            Scope sc(c, s, "reconstruct", prof, true);
-            launch_reconstruct(dj, nd, T.tlo[d], T.thi[d], tz,
-                               predict_grid(c, tz, T.thi[d] - T.tlo[d], true),
-                               depth_counters(L, d), s);
-        }
+        Scope sc(c, s, "reconstruct", prof, true);
+        launch_reconstruct(L.d_jobs + T.jlo[k], T.jhi[k] - T.jlo[k], T.tlo[k], T.thi[k], k,
+                           predict_grid(c, k, T.thi[k] - T.tlo[k], true), s);
     }
     c->chain = nullptr;
     launch_gather_results(L.d_jobs, nj, L.d_res, s);
@@ -1054,17 +1024,20 @@ hiz_status enqueue(hiz_ctx *c, int kind, const Layout &L, int nj, const Totals &
     memset(&key, 0, sizeof(key));
     key.kind = kind;
     key.njobs = nj;
-    const uint64_t v[24] = {T.mm,       T.tune,    T.tiles,    T.chunks,  T.groups, T.dblk,
-                            T.out,      T.max_groups, T.max_dblk, (uint64_t)c->cus, T.lc, T.ou,
-                            (uint64_t)T.jlo[0], (uint64_t)T.jlo[1], (uint64_t)T.jlo[2],
-                            (uint64_t)T.jhi[0], (uint64_t)T.jhi[1], (uint64_t)T.jhi[2],
-                            T.tlo[0],   T.tlo[1],  T.tlo[2],   T.thi[0],  T.thi[1], T.thi[2]};
+    uint64_t v[12 + 4 * kTileKinds] = {T.mm,   T.tune, T.tiles,      T.chunks,   T.groups,         T.dblk,
+                                       T.out,  T.max_groups, T.max_dblk, (uint64_t)c->cus, T.lc, T.ou};
+    for (int k = 0; k < kTileKinds; k++) {
+        v[12 + 4 * k] = (uint64_t)T.jlo[k];
+        v[13 + 4 * k] = (uint64_t)T.jhi[k];
+        v[14 + 4 * k] = T.tlo[k];
+        v[15 + 4 * k] = T.thi[k];
+    }
     memcpy(key.v, v, sizeof(v));
     key.ws = c->ws;
     key.pinned = c->pinned;
     // occupancy queries stay outside the capture
-    for (int tz = 1; tz <= 4; tz *= 2)
-        predict_grid(c, tz, 1, kind == 1);
+    for (int k = 0; k < kTileKinds; k++)
+        predict_grid(c, k, 1, kind == 1);
     encode_grid(c);
     GraphSlot *hit = nullptr;
     for (GraphSlot &g : c->gslot)
@@ -1186,7 +1159,7 @@ hiz_status submit_compress(hiz_ctx *c, int n, const float *const *d_fields, cons
     B.njobs = (int)jobs.size();
     if (B.njobs) {
         std::vector<uint64_t> none;
-        order_by_depth(jobs, B.field, none);
+        order_by_kind(jobs, B.field, none);
         Totals T;
         Layout L;
         rc = layout(c, jobs, false, T, L);
@@ -1293,7 +1266,7 @@ hiz_status submit_decompress(hiz_ctx *c, int n, const void *const *d_ins,
         return abandon(c, s, fail(c, HIZ_ERR_HIP, "fill launch failed"));
     B.njobs = (int)jobs.size();
     if (B.njobs) {
-        order_by_depth(jobs, B.field, B.n_out);
+        order_by_kind(jobs, B.field, B.n_out);
         Totals T;
         Layout L;
         rc = layout(c, jobs, true, T, L);
@@ -1432,14 +1405,15 @@ hiz_status compress_noalloc(hiz_ctx *c, const float *d_field, const uint64_t dim
     Totals T;
     Sections o;
     take_sections(A, J, false, T, o);
-    depth_ranges(&J, 1, T);
+    kind_ranges(&J, 1, T);
     if (!totals_fit(T))
         return fail(c, HIZ_ERR_ARG, "field too large for one launch");
-    if (A.off > kScratchBytes)
+    const uint64_t need = A.off + tile_allowance(J);
+    if (need > kScratchBytes)
         return fail(c, HIZ_ERR_ARG,
                     "field needs %llu bytes of workspace; the allocation-free call holds at most "
                     "%llu (use hiz_compress)",
-                    (unsigned long long)A.off, (unsigned long long)kScratchBytes);
+                    (unsigned long long)need, (unsigned long long)kScratchBytes);
     const uint64_t job_bytes = (sizeof(Job) + 255) & ~uint64_t(255);
     if (job_bytes + kResultBytes > c->pinned_size)
         return fail(c, HIZ_ERR_ARG, "the context's staging block is too small");
@@ -1512,8 +1486,8 @@ hiz_status hiz_create(int device, size_t workspace_bytes, hiz_ctx **out)
         delete c;
         return HIZ_ERR_HIP;
     }
-    for (int tz = 1; tz <= 4; tz *= 2)
-        predict_grid(c, tz, 1, false);
+    for (int k = 0; k < kTileKinds; k++)
+        predict_grid(c, k, 1, false);
     encode_grid(c);
     c->err.reserve(512);
     *out = c;
@@ -1578,11 +1552,11 @@ uint64_t hiz_workspace_bound(const uint64_t dims[3])
     const uint64_t tiles = cdiv(dims[0], kAnchor) * cdiv(dims[1], kAnchor) * cdiv(dims[2], kAnchor);
     const uint64_t mm = std::max<uint64_t>(cdiv(N, kMmUnit), tiles);
     const uint64_t per_job = sizeof(Job) + kResultBytes + sizeof(FieldState) + 12 * 256;
-    // per-tile coarse-level slots (values and codes of the even-point grid)
+    // per-tile allowance
     uint64_t coarse = 0;
     for (int tz = 1; tz <= 4; tz *= 2) {
         const uint64_t nt = (dims[0] / kAnchor) * (dims[1] / kAnchor) * (dims[2] / kAnchor / tz);
-        coarse = std::max(coarse, nt * (4 * coarse_values_per_tile(tz) + coarse_codes_per_tile(tz)));
+        coarse = std::max(coarse, nt * tile_allowance(tz));
     }
     // the lossless pipelines: reordered code sequence, the ratio mode's
     // payload, stage and outlier-unit look-back words (with their gaps)
@@ -1620,11 +1594,10 @@ uint64_t workspace_bound_points(uint64_t n)
     const uint64_t b = hiz_workspace_bound(d);
     if (b == 0)
         return 0;
-    // a tile of 16 x 16 x 16 tz owned points has one slot
+    // one allowance per tile of 16 x 16 x 16 tz owned points
     uint64_t coarse = 0;
     for (int tz = 1; tz <= 4; tz *= 2)
-        coarse = std::max<uint64_t>(coarse, n / (4096ull * tz) * (4 * coarse_values_per_tile(tz) +
-                                                                 coarse_codes_per_tile(tz)));
+        coarse = std::max<uint64_t>(coarse, n / (4096ull * tz) * tile_allowance((uint64_t)tz));
     return b + coarse;
 }
 } // namespace hiz
