@@ -104,7 +104,8 @@ struct Job {
     uint8_t *codes;      // N-byte code workspace
     FieldState *st;
     DecTables *dt;
-    uint64_t *lb_a;      // look-back status words (encoder groups: payload words; decoder blocks)
+    uint64_t *lb_a;      // encoder: look-back status words of the groups (payload words); decoder:
+                         // payload words of each sub-block
     uint64_t *lb_b;      // look-back status words (encoder groups: outliers)
     uint64_t *woff;      // encoder: payload word offset of each chunk
     uint64_t *zoff;      // encoder: first outlier slot of each chunk
@@ -165,7 +166,6 @@ constexpr int kFlatDepth = 4;
 // Counters reset at the start of every call.
 struct Counters {
     uint32_t enc_next;
-    uint32_t dec_next;
     uint32_t lc_next;      // bitwise-redundancy chunks
     uint32_t ou_next;      // outlier units
 };
@@ -194,14 +194,14 @@ void launch_fill(float *out, uint64_t n, float v, hipStream_t s);
 void launch_gather_results(const Job *d_jobs, int njobs, void *d_dst, hipStream_t s);
 void launch_init_decompress(const Job *d_jobs, int njobs, uint64_t max_blocks, Counters *cnt,
                             hipStream_t s);
-void launch_dec_tables(const Job *d_jobs, int njobs, hipStream_t s);
+void launch_dec_tables(const Job *d_jobs, int njobs, uint64_t max_blocks, hipStream_t s);
 // The decoder's work units are sub-blocks of kDecSub chunks, an even number
 // per field, so that a workgroup of 2 * kDecSub lanes can take a pair of one
 // field. `cus` picks the workgroup size: kDecSub lanes (one workgroup per
 // unit) while the units fit the compute units, else 2 * kDecSub.
 constexpr int kDecSub = 256;
 __host__ __device__ inline uint64_t dec_subblocks(uint64_t chunks) { return 2 * cdiv(chunks, 2 * kDecSub); }
-void launch_decode(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, int cus, hipStream_t s);
+void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, int cus, hipStream_t s);
 void launch_scatter(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s);
 void launch_reconstruct(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int kind, int grid,
                         hipStream_t s);

@@ -1,8 +1,8 @@
 // Lossless stage: Huffman coding of the one-byte quantization codes
 // (Sec. 5.2.2-5.2.3) -- codebook on the device, chunk-parallel bit-packing with
 // a single-pass decoupled look-back for chunk offsets and outlier positions,
-// table-driven chunk-parallel decoding, and the outlier scatter of
-// decompression.
+// table-driven decoding with several lanes or one to a chunk, and the outlier
+// scatter of decompression.
 #include "hiz_internal.h"
 
 #include <type_traits>
@@ -707,8 +707,6 @@ __global__ __launch_bounds__(256) void k_init_decompress(const Job *__restrict__
         if (blockIdx.y == 0 && t < sizeof(Counters) / 4)
             reinterpret_cast<uint32_t *>(cnt)[t] = 0u;
     }
-    for (uint64_t i = blockIdx.x * 256ull + t; i < J.n_dblk; i += 256ull * gridDim.x)
-        J.lb_a[i] = 0;
     for (uint64_t i = blockIdx.x * 256ull + t; i < J.n_lc; i += 256ull * gridDim.x)
         J.lb_c[i] = 0;
 }
@@ -729,7 +727,9 @@ void launch_init_decompress(const Job *d_jobs, int njobs, uint64_t max_blocks, C
 // lookup table of up to two codes within kLutBits bits, and per-length ranges
 // for longer codes. The lookup table is built by kDecTableParts workgroups
 // per field, one slice each (one entry per thread); the first also writes
-// the per-length tables.
+// the per-length tables. Further workgroups add up the payload words of the
+// field's sub-blocks of kDecSub chunks, a wave to a sub-block: a decoder
+// workgroup finds its payload by adding up the sums before its own.
 constexpr int kDecTableParts = 32;
 
 __global__ __launch_bounds__(256) void k_dec_tables(const Job *__restrict__ jobs, int njobs)
@@ -742,6 +742,23 @@ __global__ __launch_bounds__(256) void k_dec_tables(const Job *__restrict__ jobs
     __shared__ uint32_t index[kMaxCodeLen + 2];
     __shared__ uint8_t s_sorted[256];
     const int t = threadIdx.x;
+    if (blockIdx.x >= kDecTableParts) {
+        const uint64_t sub = (uint64_t)(blockIdx.x - kDecTableParts) * 4 + (t >> 6);
+        if (sub >= J.n_dblk)
+            return;
+        HIZ_GLOBAL const uint32_t *counts =
+            reinterpret_cast<HIZ_GLOBAL const uint32_t *>(gmem(J.stream) + kOffChunks);
+        uint64_t n = 0;
+#pragma unroll
+        for (int k = 0; k < kDecSub / 64; k++) {
+            const uint64_t c = sub * kDecSub + 64 * k + (t & 63);
+            n += c < J.n_chunks ? min(counts[c], J.chunk) : 0u;
+        }
+        n = wave_sum64(n);
+        if ((t & 63) == 0)
+            J.lb_a[sub] = n;
+        return;
+    }
     len[t] = gmem(J.stream)[kOffLen + t];
     if (t < kMaxCodeLen + 2)
         blc[t] = 0;
@@ -812,14 +829,36 @@ __global__ __launch_bounds__(256) void k_dec_tables(const Job *__restrict__ jobs
     }
 }
 
-void launch_dec_tables(const Job *d_jobs, int njobs, hipStream_t s)
+void launch_dec_tables(const Job *d_jobs, int njobs, uint64_t max_blocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dec_tables, dim3(kDecTableParts, njobs), dim3(256), 0, s, d_jobs, njobs);
+    hipLaunchKernelGGL(k_dec_tables, dim3((uint32_t)(kDecTableParts + cdiv(max_blocks, 4)), njobs),
+                       dim3(256), 0, s, d_jobs, njobs);
+}
+
+// Payload words before chunk `first` of a field (its chunk counts taken as the
+// sums above take them), for the whole workgroup; `red`: a word per wave.
+__device__ inline uint64_t words_before(const Job &J, HIZ_GLOBAL const uint32_t *counts,
+                                        uint64_t first, uint64_t *red)
+{
+    const uint64_t sub = first / kDecSub;
+    uint64_t n = 0;
+    for (uint64_t i = threadIdx.x; i < sub; i += blockDim.x)
+        n += gmem(J.lb_a)[i];
+    const uint64_t c = sub * kDecSub + threadIdx.x;
+    if (threadIdx.x < kDecSub && c < first)
+        n += min(counts[c], J.chunk);
+    n = wave_sum64(n);
+    if ((threadIdx.x & 63) == 0)
+        red[threadIdx.x >> 6] = n;
+    __syncthreads();
+    n = 0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); w++)
+        n += red[w];
+    return n;
 }
 
 // One thread per chunk; a workgroup takes kDecChunks consecutive chunks
-// (one or two sub-blocks of one field), finds its payload offset by
-// look-back over the stored word counts, and each thread decodes its chunk
+// (one or two sub-blocks of one field), and each thread decodes its chunk
 // sequentially with the LDS lookup table, up to two codes per table read.
 constexpr int kRing = 32;      // payload words of a decoder lane's LDS ring (a power of two)
 constexpr int kRowRing = 64;   // a lane's LDS output ring of codes (a power of two)
@@ -828,7 +867,7 @@ constexpr int kFlush = 32;     // codes a lane stores at once: one 32-byte align
 
 template <int kDecChunks>
 __global__ __launch_bounds__(kDecChunks) void k_decode(const Job *__restrict__ jobs, int njobs,
-                                                       uint64_t total, Counters *cnt)
+                                                       uint64_t total)
 {
     static_assert(kDecChunks % kDecSub == 0 && kDecChunks >= 256, "whole sub-blocks");
     constexpr int kWaves = kDecChunks / 64;
@@ -836,19 +875,13 @@ __global__ __launch_bounds__(kDecChunks) void k_decode(const Job *__restrict__ j
     __shared__ __align__(16) uint32_t lut[1 << kLutBits];
     __shared__ uint32_t limit[kMaxCodeLen + 2], base[kMaxCodeLen + 2];
     __shared__ uint8_t sorted[256];
-    __shared__ uint32_t s_id, s_maxlen;
-    __shared__ uint64_t s_wsum[kWaves];
-    __shared__ uint64_t s_base;
+    __shared__ uint32_t s_maxlen;
+    __shared__ uint64_t s_wsum[kWaves], s_red[kWaves];
     __shared__ uint32_t s_win[kDecChunks * kRing];
     __shared__ __align__(16) uint8_t s_rows[kDecChunks * kRowBytes];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    if (t == 0)
-        s_id = atomicAdd(&cnt->dec_next, 1u);
-    __syncthreads();
     // total counts sub-blocks; each field has an even number of them
-    const uint64_t id = s_id;
-    if (id * kSubs >= total)
-        return;
+    const uint64_t id = blockIdx.x;
     const Job &J = jobs[find_job<WK_DBLK>(jobs, njobs, id * kSubs)];
     const DecTables *dt = J.dt;
     {
@@ -865,7 +898,7 @@ __global__ __launch_bounds__(kDecChunks) void k_decode(const Job *__restrict__ j
         sorted[t] = dt->sorted[t];
     if (t == 0)
         s_maxlen = dt->maxlen;
-    // this workgroup's place among the field's workgroups (the look-back index)
+    // this workgroup's place among the field's workgroups
     const uint64_t lb = (id * kSubs - J.dblk_begin) / kSubs;
     const uint64_t chunk = lb * kDecChunks + t;
     HIZ_GLOBAL const uint32_t *counts =
@@ -879,22 +912,14 @@ __global__ __launch_bounds__(kDecChunks) void k_decode(const Job *__restrict__ j
     const uint64_t incl = wave_incl_scan64(wc);
     if (lane == 63)
         s_wsum[wv] = incl;
-    __syncthreads();
-    uint64_t before = 0, blk_total = 0;
-    for (int k = 0; k < kWaves; k++) {
+    const uint64_t base_words = words_before(J, counts, lb * kDecChunks, s_red);
+    uint64_t before = 0;
+    for (int k = 0; k < kWaves; k++)
         before += (k < wv) ? s_wsum[k] : 0;
-        blk_total += s_wsum[k];
-    }
-    if (wv == 0) {
-        const uint64_t b = lookback(J.lb_a, lb, blk_total);
-        if (lane == 0)
-            s_base = b;
-    }
-    __syncthreads();
     if (chunk >= J.n_chunks)
         return;
     FieldState *st = J.st;
-    const uint64_t start = s_base + before + incl - wc;
+    const uint64_t start = base_words + before + incl - wc;
     const uint64_t pw = J.payload_words;
     if (pw == 0 || start + wc > pw) {
         atomicOr(&st->flags, (uint32_t)ST_CORRUPT);
@@ -1237,20 +1262,285 @@ __global__ __launch_bounds__(kDecChunks) void k_decode(const Job *__restrict__ j
         atomicAdd((unsigned long long *)&st->zeros_seen, (unsigned long long)zeros);
 }
 
-void launch_decode(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, int cus, hipStream_t s)
+// G lanes per chunk, for calls of too few chunks to fill the chip with one lane
+// each (a lane's 1024 codes one after the other take 130 to 440 us, however few
+// chunks there are). Prefix codes fall into step: a reader that starts at any bit is
+// soon at the true code boundaries. So lane j of a chunk reads the j-th G-th of
+// its bits [j B, (j + 1) B):
+//  1. from kSync average codes ahead of its part, up to the first code that
+//     starts in its part: where it starts;
+//  2. on to the first code that starts past its part: where it ends, and its
+//     codes are counted. Where the lane before ended elsewhere than this one
+//     started, this one starts there and reads its part again, until all agree
+//     (a lane's start is right once the lanes before it are, and lane 0's is);
+//  3. the counts before it give its place in the chunk, and it reads its part
+//     once more, for the symbols.
+// The payload of a wave's chunks is staged in LDS (or, where it is longer than
+// most, read from memory), so is the chunk's output, stored 16 bytes a lane.
+// Every step takes the bits at its position anew: no state but the position.
+// What bounds it: the instructions of a step (35 for the symbols) and its LDS
+// reads at random, at four waves per SIMD. 16 M codes with 16 lanes per chunk 66
+// us, 262144 codes with 64 lanes 28 us; one lane per chunk took 180 us for both.
+constexpr int kSplitMax = 1024; // longest chunk
+constexpr int kSync = 16;
+
+template <int G, int NT>
+__global__ __launch_bounds__(NT) void k_decode_split(const Job *__restrict__ jobs, int njobs)
+{
+    constexpr int kWaves = NT / 64, PW = 64 / G, PB = NT / G; // chunks per wave, workgroup
+    constexpr int kUnits = kDecSub / PB;                      // workgroups per sub-block
+    constexpr int kStage = G == 64 ? kSplitMax + 4 : 240 * PW; // payload words of a wave
+    constexpr int kOut = kSplitMax + 16;                       // a chunk's output: slot C takes what is past it
+    __shared__ __align__(16) uint32_t lut[1 << kLutBits];
+    __shared__ uint32_t base[kMaxCodeLen + 2];
+    __shared__ uint8_t sorted[256];
+    __shared__ uint64_t s_red[kWaves];
+    __shared__ uint32_t s_stage[kWaves][kStage];
+    __shared__ __align__(16) uint8_t s_out[kWaves][PW * kOut];
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const Job &J = jobs[find_job<WK_DBLK>(jobs, njobs, blockIdx.x / kUnits)];
+    const uint64_t first = (blockIdx.x - J.dblk_begin * kUnits) * PB; // the workgroup's first chunk
+    if (first >= J.n_chunks)
+        return;
+    const DecTables *dt = J.dt;
+    {
+        HIZ_GLOBAL const uint8_t *src = reinterpret_cast<HIZ_GLOBAL const uint8_t *>(gmem(dt->lut));
+        uint4 *dst = reinterpret_cast<uint4 *>(lut);
+#pragma unroll
+        for (int i = 0; i < (1 << kLutBits) / 4 / NT; i++)
+            dst[t + i * NT] = gload_u4(src + 16 * (t + i * NT));
+    }
+    if (t <= kMaxCodeLen)
+        base[t] = dt->base[t];
+    if (t < 256)
+        sorted[t] = dt->sorted[t];
+    HIZ_GLOBAL const uint32_t *counts =
+        reinterpret_cast<HIZ_GLOBAL const uint32_t *>(gmem(J.stream) + kOffChunks);
+    const uint32_t maxlen = (uint32_t)__builtin_amdgcn_readfirstlane((int)dt->maxlen);
+    // ends of the code ranges of the lengths past the table, less one (all
+    // ones for the lengths not used)
+    uint32_t lim[kMaxCodeLen - kLutBits - 1];
+#pragma unroll
+    for (int k = 0; k < kMaxCodeLen - kLutBits - 1; k++) {
+        const int L = kLutBits + 1 + k;
+        lim[k] = (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)((uint32_t)L < maxlen ? dt->limit[L] - 1u : 0xFFFFFFFFu));
+    }
+    // words of the workgroup's chunks, chunk i in lane i of every wave
+    const uint64_t ci = first + lane;
+    const uint32_t raw = lane < PB && ci < J.n_chunks ? counts[ci] : 0u;
+    const uint32_t mine = min(raw, J.chunk);
+    const uint32_t incl = wave_incl_scan_dpp(mine);
+    const uint64_t wbase = words_before(J, counts, first, s_red); // also: the tables are in LDS
+    FieldState *st = J.st;
+    const uint64_t pw = J.payload_words;
+    bool bad = wv == 0 && raw > J.chunk;
+
+    // this lane's chunk
+    const int sub = lane / G, j = lane % G, cl = wv * PW + sub;
+    const uint64_t ck = first + cl;
+    const uint32_t rel0 = __shfl(incl, wv * PW, 64) - __shfl(mine, wv * PW, 64); // the wave's first word
+    const uint32_t wrel = __shfl(incl, cl, 64) - __shfl(mine, cl, 64);           // the chunk's
+    uint32_t wc = __shfl(mine, cl, 64);
+    const uint64_t start = wbase + wrel;
+    uint32_t nsym = 0;
+    if (ck < J.n_chunks) {
+        nsym = (uint32_t)(min((ck + 1) << J.log2_chunk, J.N) - (ck << J.log2_chunk));
+        bad |= start + wc > pw || (ck == J.n_chunks - 1 && start + wc != pw);
+        if (start + wc > pw)
+            wc = 0;
+    }
+    HIZ_GLOBAL const uint32_t *words =
+        (J.pipe == PIPE_CR ? reinterpret_cast<HIZ_GLOBAL const uint32_t *>(gmem(J.hpay))
+                           : reinterpret_cast<HIZ_GLOBAL const uint32_t *>(gmem(J.stream) + J.off_payload)) +
+        wbase + rel0;
+    const uint64_t left64 = pw > wbase + rel0 ? pw - wbase - rel0 : 0; // payload words from there on
+    const uint32_t left = (uint32_t)min(left64, (uint64_t)0x7FFFFFFF);
+    const uint32_t nw = __shfl(incl, wv * PW + PW - 1, 64) - rel0; // the wave's words
+    const bool fits = nw + 1 <= (uint32_t)kStage;
+    uint32_t *stage = s_stage[wv];
+    if (fits)
+        for (uint32_t i = lane; i <= nw; i += 64)
+            stage[i] = i < left ? words[i] : 0u;
+    wave_sync_lds();
+    const uint32_t w0 = wrel - rel0; // the chunk's first word among the wave's
+
+    // the 32 bits at bit `pos` of the chunk; pos < 32 wc
+    auto window = [&](uint32_t pos) __attribute__((always_inline)) -> uint32_t {
+        const uint32_t i = w0 + (pos >> 5);
+        uint32_t a, b;
+        if (fits) {
+            a = stage[i];
+            b = stage[i + 1];
+        } else {
+            a = i < left ? words[i] : 0u;
+            b = i + 1 < left ? words[i + 1] : 0u;
+        }
+        return (uint32_t)(((((uint64_t)a << 32) | b) << (pos & 31)) >> 32);
+    };
+    // length of the code at the top of `win`, longer than the table's (past
+    // every range: maxlen + 1)
+    auto long_code = [&](uint32_t win) __attribute__((always_inline)) -> uint32_t {
+        uint32_t L = kLutBits + 1;
+#pragma unroll
+        for (int k = 0; k < kMaxCodeLen - kLutBits - 1; k++)
+            L += win > lim[k] ? 1u : 0u;
+        return L;
+    };
+    // Codes from `pos` up to the first that starts at or past `end`; returns where
+    // that is and how many codes came before it.
+    auto scan = [&](uint32_t pos, uint32_t end, bool on, uint32_t &n) __attribute__((always_inline)) -> uint32_t {
+        n = 0;
+        on = on && pos < end;
+        while (__any(on)) {
+            if (on) {
+                const uint32_t win = window(pos), e = lut[win >> (32 - kLutBits)];
+                uint32_t len = (0u - e) & 31u, one = e >> 24, m = (e >> 5) & 3u;
+                if (e == 0u) {
+                    const uint32_t L = long_code(win);
+                    len = one = L > maxlen ? 1u : L;
+                    m = 1;
+                }
+                // the second code counts when it starts before the end
+                const bool first_only = pos + one >= end;
+                pos += first_only ? one : len;
+                n += first_only ? 1u : m;
+                on = pos < end;
+            }
+        }
+        return pos;
+    };
+    const uint32_t bits = 32 * wc, B = (bits + G - 1) / G;
+    const uint32_t lo = min(j * B, bits), hi = min(lo + B, bits);
+    const uint32_t ahead = nsym ? kSync * bits / nsym + 1 : 0;
+    // `mid`: where a second reading of the part is expected to be in step with
+    // the first; from there on it is not read again
+    const uint32_t mid = min(lo + ahead, hi);
+    uint32_t n, n0, at = lo > ahead ? lo - ahead : 0u;
+    at = scan(at, lo, true, n);
+    uint32_t in = scan(at, mid, true, n0), to = scan(in, hi, true, n);
+    for (;;) {
+        const uint32_t prev = (uint32_t)__shfl_up((int)to, 1, 64);
+        const bool wrong = j > 0 && prev != at;
+        if (!__any(wrong))
+            break;
+        if (wrong)
+            at = prev;
+        uint32_t m0, m;
+        const uint32_t in2 = scan(at, mid, wrong, m0);
+        const bool apart = wrong && in2 != in;
+        const uint32_t to2 = scan(in2, hi, apart, m);
+        if (wrong)
+            n0 = m0;
+        if (apart) {
+            in = in2;
+            to = to2;
+            n = m;
+        }
+    }
+    n += n0;
+    // this lane's place in the chunk
+    uint32_t pos_incl = n;
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)pos_incl, o, 64);
+        pos_incl += j >= o ? u : 0u;
+    }
+    if (j == G - 1 && pos_incl < nsym)
+        bad = true;
+    // the symbols; those past the chunk's last one are padding
+    uint8_t *out = s_out[wv] + sub * kOut;
+    uint32_t idx = pos_incl - n, pos = at;
+    bool on = pos < hi && idx < nsym;
+    while (__any(on)) {
+        if (on) {
+            const uint32_t win = window(pos), e = lut[win >> (32 - kLutBits)];
+            uint32_t len = (0u - e) & 31u, one = e >> 24, m = (e >> 5) & 3u, s1 = (e >> 8) & 255u;
+            if (e == 0u) {
+                const uint32_t L = long_code(win);
+                m = 1;
+                if (L > maxlen) {
+                    bad = true;
+                    len = one = 1;
+                    s1 = 0;
+                } else {
+                    len = one = L;
+                    s1 = sorted[(base[L] + (win >> (32 - L))) & 255u];
+                }
+            }
+            // (the last symbol's own end is what the word count is checked by)
+            const bool first_only = pos + one >= hi || idx + 1 >= nsym;
+            const bool two = !first_only && m == 2;
+            out[idx] = (uint8_t)s1;
+            out[two ? idx + 1 : (uint32_t)kSplitMax] = (uint8_t)(e >> 16);
+            pos += first_only ? one : len;
+            idx += two ? 2u : 1u;
+            if (idx == nsym && (pos + 31) / 32 != wc)
+                bad = true;
+            on = pos < hi && idx < nsym;
+        }
+    }
+    wave_sync_lds();
+    // codes to memory, code-0 points counted on the way
+    uint32_t zeros = 0;
+    const uint64_t i0 = (first + wv * PW) << J.log2_chunk;
+    const uint32_t C = J.chunk;
+    HIZ_GLOBAL uint8_t *codes = gmem(J.seq);
+    for (uint32_t i = 16 * lane; i < PW * C; i += 16 * 64) {
+        const uint32_t c = i >> J.log2_chunk, r = i & (C - 1);
+        const uint4 v = *reinterpret_cast<const uint4 *>(s_out[wv] + c * kOut + r);
+        if (i0 + i >= J.N)
+            break;
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        const int valid = (int)min(J.N - i0 - i, (uint64_t)16);
+        if (valid == 16)
+            gstore_u4(codes + i0 + i, v);
+        else
+            for (int k = 0; k < valid; k++)
+                codes[i0 + i + k] = (uint8_t)((k < 4 ? w[0] : (k < 8 ? w[1] : (k < 12 ? w[2] : w[3]))) >> (8 * (k & 3)));
+        zeros += zero_codes(w, valid);
+    }
+    if (bad)
+        atomicOr(&st->flags, (uint32_t)ST_CORRUPT);
+    for (int o = 32; o > 0; o >>= 1)
+        zeros += (uint32_t)__shfl_xor((int)zeros, o, 64);
+    if (lane == 0 && zeros)
+        atomicAdd((unsigned long long *)&st->zeros_seen, (unsigned long long)zeros);
+}
+
+// total: the call's sub-blocks of kDecSub chunks; longest: its longest chunk.
+void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, int cus, hipStream_t s)
 {
     if (total == 0)
         return;
+    // Several lanes per chunk, the fewer the more chunks there are: the work
+    // they add (reading parts twice, ahead of their start) only pays while the
+    // chip has idle lanes. Measured decode times, us, with 64 / 32 / 16 lanes and
+    // one lane per chunk: 1 sub-block (64^3) 28 / 36 / 65 / 179; 8 sub-blocks 24 /
+    // 32 / 49 / 156; 25: 57 / 32 / 49 / 132; 62: 155 / 80 / 66 / 180; 250: 450 / 207 /
+    // 195 / 200; 512 (512^3): 900 / 420 / 420 / 201.
+    if (longest <= (uint32_t)kSplitMax && total <= (uint64_t)cus) {
+        if (total <= (uint64_t)cus / 16)
+            hipLaunchKernelGGL((k_decode_split<64, 256>), dim3((uint32_t)(total * 64)), dim3(256), 0, s,
+                               d_jobs, njobs);
+        else if (total <= (uint64_t)cus / 8)
+            hipLaunchKernelGGL((k_decode_split<32, 512>), dim3((uint32_t)(total * 16)), dim3(512), 0, s,
+                               d_jobs, njobs);
+        else
+            hipLaunchKernelGGL((k_decode_split<16, 1024>), dim3((uint32_t)(total * 4)), dim3(1024), 0, s,
+                               d_jobs, njobs);
+        return;
+    }
     // one workgroup of kDecSub lanes per compute unit while the sub-blocks
     // fit the device; past that, workgroups of two sub-blocks share one
     // table among twice the lanes (one workgroup per compute unit either
     // way, by their LDS)
     if (total <= (uint64_t)cus)
         hipLaunchKernelGGL(k_decode<kDecSub>, dim3((uint32_t)total), dim3(kDecSub), 0, s, d_jobs,
-                           njobs, total, cnt);
+                           njobs, total);
     else
         hipLaunchKernelGGL(k_decode<2 * kDecSub>, dim3((uint32_t)(total / 2)), dim3(2 * kDecSub), 0,
-                           s, d_jobs, njobs, total, cnt);
+                           s, d_jobs, njobs, total);
 }
 
 // Outliers go to their positions in the output before reconstruction reads

@@ -45,7 +45,7 @@ struct Pending {
 struct GraphKey {
     int kind; // 0 compress, 1 decompress
     int njobs;
-    uint64_t v[12 + 4 * kTileKinds];
+    uint64_t v[13 + 4 * kTileKinds];
     const void *ws;
     const void *pinned;
 };
@@ -729,6 +729,7 @@ void plan_decompress(const Parsed &P, const void *d_in, uint64_t in_size, float 
 struct Totals {
     uint64_t mm = 0, tune = 0, tiles = 0, chunks = 0, groups = 0, dblk = 0, out = 0;
     uint64_t max_groups = 0, max_dblk = 0;
+    uint32_t max_chunk = 0;    // longest Huffman chunk
     uint64_t lc = 0, ou = 0;   // stage chunks, outlier units
     uint64_t max_n = 0;        // largest field (reordering launch)
     bool reorder = false;      // some field's codes are reordered
@@ -784,6 +785,7 @@ void take_sections(Arena &A, Job &J, bool decompress, Totals &T, Sections &o)
         T.dblk += J.n_dblk;
         T.out += J.n_out;
         T.max_dblk = std::max(T.max_dblk, J.n_dblk);
+        T.max_chunk = std::max(T.max_chunk, J.chunk);
     } else {
         o.lba = A.take(8 * J.n_groups);
         o.lbb = A.take(8 * J.n_groups);
@@ -972,11 +974,11 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
     c->chain = nullptr;
     {
         Scope sc(c, s, "init_dec", prof, true);
-        launch_init_decompress(L.d_jobs, nj, std::max(T.max_dblk, T.max_clear), L.d_cnt, s);
+        launch_init_decompress(L.d_jobs, nj, T.max_clear, L.d_cnt, s);
     }
     if (T.dblk) {
         Scope sc(c, s, "dec_tables", prof, true);
-        launch_dec_tables(L.d_jobs, nj, s);
+        launch_dec_tables(L.d_jobs, nj, T.max_dblk, s);
     }
     if (T.lc) {
         Scope sc(c, s, "lc_decode", prof, true);
@@ -984,7 +986,7 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
     }
     if (T.dblk) {
         Scope sc(c, s, "decode", prof, true);
-        launch_decode(L.d_jobs, nj, T.dblk, L.d_cnt, c->cus, s);
+        launch_decode(L.d_jobs, nj, T.dblk, T.max_chunk, c->cus, s);
     }
     if (T.reorder) {
         Scope sc(c, s, "unreorder", prof, true);
@@ -1024,13 +1026,14 @@ hiz_status enqueue(hiz_ctx *c, int kind, const Layout &L, int nj, const Totals &
     memset(&key, 0, sizeof(key));
     key.kind = kind;
     key.njobs = nj;
-    uint64_t v[12 + 4 * kTileKinds] = {T.mm,   T.tune, T.tiles,      T.chunks,   T.groups,         T.dblk,
-                                       T.out,  T.max_groups, T.max_dblk, (uint64_t)c->cus, T.lc, T.ou};
+    uint64_t v[13 + 4 * kTileKinds] = {T.mm,   T.tune, T.tiles,      T.chunks,   T.groups,         T.dblk,
+                                       T.out,  T.max_groups, T.max_dblk, (uint64_t)c->cus, T.lc, T.ou,
+                                       T.max_chunk};
     for (int k = 0; k < kTileKinds; k++) {
-        v[12 + 4 * k] = (uint64_t)T.jlo[k];
-        v[13 + 4 * k] = (uint64_t)T.jhi[k];
-        v[14 + 4 * k] = T.tlo[k];
-        v[15 + 4 * k] = T.thi[k];
+        v[13 + 4 * k] = (uint64_t)T.jlo[k];
+        v[14 + 4 * k] = (uint64_t)T.jhi[k];
+        v[15 + 4 * k] = T.tlo[k];
+        v[16 + 4 * k] = T.thi[k];
     }
     memcpy(key.v, v, sizeof(v));
     key.ws = c->ws;
