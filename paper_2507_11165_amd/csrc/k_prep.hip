@@ -3,6 +3,8 @@
 // sampled-block tuner (Sec. 5.1.3).
 #include "hiz_internal.h"
 
+#include <type_traits>
+
 namespace hiz {
 
 // ---------------------------------------------------------------------------
@@ -190,11 +192,16 @@ void launch_eps(const Job *d_jobs, int njobs, hipStream_t s)
 // more thread blocks: per sample, one block tests strides 8 and 4, two
 // blocks share stride 2 and six share stride 1. Unlike the paper, each block
 // tests all 21 candidates on its share of targets, because the candidates
-// reuse the same per-axis stencils.
+// reuse the same per-axis stencils: a sequential candidate predicts a target by
+// one axis's stencil, the last of its odd axes in the candidate's order. So a
+// target costs three splines' errors along each of its odd axes and, with more
+// than one, of their combination; they are added up apart for each class of
+// targets (which axes are odd) and handed out to the candidates once per class.
+// What bounds it is the latency of one workgroup: with all 21 errors formed per
+// target 26 us at 64^3, 39 at 512^3 and 28 for a 1800 x 3600 field; this way 21,
+// 28 and 18.
 // ---------------------------------------------------------------------------
 constexpr int kTuneParts = 9;
-
-__constant__ int8_t c_perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
 
 // 1-D spline stencil (Sec. 5.1.2): Lagrange weights at the midpoint from the
 // samples at -3s, -s, +s, +3s; lower orders where samples are missing. With
@@ -249,81 +256,115 @@ __device__ __forceinline__ float md_combine(const float p[3], const int r[3], in
     return ((p[0] + p[1]) + p[2]) / 3.0f;
 }
 
+// |x - p| in units of 1 / scale, rounded and capped at 2^36, as the integer held
+// in the low bits of 2^52 + it: sums of n terms carry n times 2^52's bits
+// (kTermBias), taken off at the end. A NaN counts as the cap.
+constexpr uint64_t kTermBias = 0x4330000000000000ull;
 __device__ __forceinline__ uint64_t tune_term(float x, float p, double scale)
 {
-    float e = fabsf(x - p);
-    double w = (double)e * scale;
-    const double cap = 68719476736.0; // 2^36
-    return (w < cap) ? (uint64_t)(w + 0.5) : (uint64_t)cap;
+    const double w = fmin((double)fabsf(x - p) * scale, 68719476736.0);
+    return (uint64_t)__double_as_longlong(trunc(w + 0.5) + 4503599627370496.0);
 }
 
-__device__ inline uint64_t wave_sum_u64(uint64_t v)
+// Sum over the wave with DPP moves (the result in lane 63).
+__device__ __forceinline__ uint64_t wave_sum_dpp64(uint64_t v)
 {
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-        lo = (uint32_t)__shfl_xor((int)lo, o, 64);
-        hi = (uint32_t)__shfl_xor((int)hi, o, 64);
+    auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+        constexpr int c = decltype(ctrl)::value, r = decltype(rows)::value;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, c, r, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), c, r, 0xf, false);
         v += ((uint64_t)hi << 32) | lo;
-    }
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{}); // row_shr 1
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{}); // row_bcast 15
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{}); // row_bcast 31
     return v;
 }
 
-// Accumulate the 21 candidate error sums of the targets [g0, g1) of the
-// stride-s grid of a block held in LDS (strides 17*17, 17, 1) whose extent on
-// axis k is E[k] (17, or 1 on a flat axis).
-__device__ void tune_level(const float *__restrict__ blk, const int E[3], int s, int g0, int g1,
-                           double scale, uint64_t acc[kCands])
+// Add the 21 candidates' error sums of class M's targets on the stride-s grid of
+// a block held in LDS (strides 17*17, 17, 1) whose extent on axis k is E[k] (17,
+// or 1 on a flat axis); of the targets in order, those from n g0 / parts up to
+// n (g0 + 1) / parts.
+template <int M>
+__device__ __forceinline__ void tune_class(const float *__restrict__ blk, const int E[3], int s,
+                                           int part, int parts, double scale, uint64_t acc[kCands])
 {
-    const int Gx = E[0] == 1 ? 1 : 16 / s + 1, Gy = E[1] == 1 ? 1 : 16 / s + 1,
-              Gz = E[2] == 1 ? 1 : 16 / s + 1;
-    for (int g = g0 + (int)threadIdx.x; g < g1; g += blockDim.x) {
-        int iz = g % Gz, r = g / Gz, iy = r % Gy, ix = r / Gy;
-        int mask = (ix & 1) | ((iy & 1) << 1) | ((iz & 1) << 2);
-        if (mask == 0)
-            continue;
-        int t[3] = {ix * s, iy * s, iz * s};
+    const int K = 8 / s; // odd multiples of s in a block; even ones: one more
+    int n[3];
+    for (int k = 0; k < 3; k++)
+        n[k] = (M >> k) & 1 ? (E[k] == 1 ? 0 : K) : (E[k] == 1 ? 1 : K + 1);
+    const int total = n[0] * n[1] * n[2];
+    constexpr bool MULTI = (M & (M - 1)) != 0;
+    uint64_t one[3][3] = {}, md[3] = {}; // [spline][axis]; multi-dimensional
+    int terms = 0;
+    for (int g = part * total / parts + (int)threadIdx.x; g < (part + 1) * total / parts;
+         g += blockDim.x) {
+        const int iz = g % n[2], r = g / n[2], iy = r % n[1], ix = r / n[1];
+        const int t[3] = {(2 * ix + (M & 1)) * s, (2 * iy + ((M >> 1) & 1)) * s,
+                          (2 * iz + (M >> 2)) * s};
         const int st[3] = {kSide * kSide, kSide, 1};
-        int li = (t[0] * kSide + t[1]) * kSide + t[2];
-        float pl[3] = {0, 0, 0}, pc3[3] = {0, 0, 0}, pn[3] = {0, 0, 0};
-        int rl[3] = {-1, -1, -1}, rc[3] = {-1, -1, -1}, rn[3] = {-1, -1, -1};
+        const int li = (t[0] * kSide + t[1]) * kSide + t[2];
+        const float x = blk[li];
+        float p[3][3];
+        int rk[3][3];
+#pragma unroll
         for (int k = 0; k < 3; k++) {
-            if (!((mask >> k) & 1))
+            if (!((M >> k) & 1))
                 continue;
-            int tk = t[k];
-            bool pa = tk - 3 * s >= 0, pcp = tk + s <= E[k] - 1, pd = tk + 3 * s <= E[k] - 1;
-            float b = blk[li - s * st[k]];
-            float a = pa ? blk[li - 3 * s * st[k]] : 0.0f;
-            float c = pcp ? blk[li + s * st[k]] : 0.0f;
-            float d = pd ? blk[li + 3 * s * st[k]] : 0.0f;
-            pl[k] = stencil_1d(a, b, c, d, pa, pcp, pd, 0, rl[k]);
-            pc3[k] = stencil_1d(a, b, c, d, pa, pcp, pd, 1, rc[k]);
-            pn[k] = stencil_1d(a, b, c, d, pa, pcp, pd, 2, rn[k]);
+            const bool pa = t[k] - 3 * s >= 0, pc = t[k] + s <= E[k] - 1, pd = t[k] + 3 * s <= E[k] - 1;
+            const float b = blk[li - s * st[k]];
+            const float a = pa ? blk[li - 3 * s * st[k]] : 0.0f;
+            const float c = pc ? blk[li + s * st[k]] : 0.0f;
+            const float d = pd ? blk[li + 3 * s * st[k]] : 0.0f;
+#pragma unroll
+            for (int sp = 0; sp < 3; sp++) {
+                p[sp][k] = stencil_1d(a, b, c, d, pa, pc, pd, sp, rk[sp][k]);
+                one[sp][k] += tune_term(x, p[sp][k], scale);
+            }
         }
-        float x = blk[li];
-        acc[0] += tune_term(x, md_combine(pl, rl, mask), scale);
-        acc[7] += tune_term(x, md_combine(pc3, rc, mask), scale);
-        acc[14] += tune_term(x, md_combine(pn, rn, mask), scale);
-        for (int perm = 0; perm < 6; perm++) {
-            int axis = -1;
-            for (int j = 0; j < 3; j++)
-                if ((mask >> c_perm[perm][j]) & 1)
-                    axis = c_perm[perm][j];
-            float vl = axis == 0 ? pl[0] : (axis == 1 ? pl[1] : pl[2]);
-            float vc = axis == 0 ? pc3[0] : (axis == 1 ? pc3[1] : pc3[2]);
-            float vn = axis == 0 ? pn[0] : (axis == 1 ? pn[1] : pn[2]);
-            acc[1 + perm] += tune_term(x, vl, scale);
-            acc[8 + perm] += tune_term(x, vc, scale);
-            acc[15 + perm] += tune_term(x, vn, scale);
+        if constexpr (MULTI)
+#pragma unroll
+            for (int sp = 0; sp < 3; sp++)
+                md[sp] += tune_term(x, md_combine(p[sp], rk[sp], M), scale);
+        terms++;
+    }
+    const uint64_t bias = (uint64_t)terms * kTermBias;
+    constexpr int first = (M & 1) ? 0 : ((M & 2) ? 1 : 2);
+#pragma unroll
+    for (int sp = 0; sp < 3; sp++) {
+        acc[7 * sp] += (MULTI ? md[sp] : one[sp][first]) - bias;
+        // SEQ over the orders (x,y,z) (x,z,y) (y,x,z) (y,z,x) (z,x,y) (z,y,x)
+        constexpr int perm[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+#pragma unroll
+        for (int q = 0; q < 6; q++) {
+            const int axis = (M >> perm[q][2]) & 1 ? perm[q][2]
+                                                   : ((M >> perm[q][1]) & 1 ? perm[q][1] : perm[q][0]);
+            acc[7 * sp + 1 + q] += one[sp][axis] - bias;
         }
     }
+}
+__device__ void tune_level(const float *__restrict__ blk, const int E[3], int s, int part, int parts,
+                           double scale, uint64_t acc[kCands])
+{
+    tune_class<1>(blk, E, s, part, parts, scale, acc);
+    tune_class<2>(blk, E, s, part, parts, scale, acc);
+    tune_class<3>(blk, E, s, part, parts, scale, acc);
+    tune_class<4>(blk, E, s, part, parts, scale, acc);
+    tune_class<5>(blk, E, s, part, parts, scale, acc);
+    tune_class<6>(blk, E, s, part, parts, scale, acc);
+    tune_class<7>(blk, E, s, part, parts, scale, acc);
 }
 
 __device__ void tune_flush(FieldState *st, int level, uint64_t acc[kCands], uint64_t *red)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
     for (int c = 0; c < kCands; c++) {
-        uint64_t v = wave_sum_u64(acc[c]);
-        if (lane == 0)
+        const uint64_t v = wave_sum_dpp64(acc[c]);
+        if (lane == 63)
             red[wave * kCands + c] = v;
         acc[c] = 0;
     }
@@ -362,34 +403,39 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
     // a full block spans 17 points per axis, 1 on a flat axis (2-D / 1-D fields)
     const int E[3] = {J.dims[0] == 1 ? 1 : kSide, J.dims[1] == 1 ? 1 : kSide,
                       J.dims[2] == 1 ? 1 : kSide};
-    for (int i = threadIdx.x; i < kSide * kSide * kSide; i += blockDim.x) {
-        int z = i % kSide, r = i / kSide, y = r % kSide, x = r / kSide;
-        if (x < E[0] && y < E[1] && z < E[2])
-            blk[i] = gmem(J.field)[((ba * kAnchor + x) * dy + (bb * kAnchor + y)) * dz +
-                                   bc * kAnchor + z];
+    // all of a thread's loads in flight before the first is written to LDS
+    constexpr int IB = (kSide * kSide * kSide + 255) / 256;
+    float e[IB];
+    HIZ_GLOBAL const float *f0 =
+        gmem(J.field) + ((ba * kAnchor) * dy + bb * kAnchor) * dz + bc * kAnchor;
+#pragma unroll
+    for (int k = 0; k < IB; k++) {
+        const int i = threadIdx.x + 256 * k;
+        const int z = i % kSide, r = i / kSide, y = r % kSide, x = r / kSide;
+        const bool in = x < E[0] && y < E[1] && z < E[2]; // (past the block's last point: x = 17)
+        e[k] = f0[in ? (x * dy + y) * dz + z : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < IB; k++) {
+        const int i = threadIdx.x + 256 * k;
+        if (k < IB - 1 || i < kSide * kSide * kSide)
+            blk[i] = e[k];
     }
     __syncthreads();
-    auto targets = [&](int s) {
-        const int g = 16 / s + 1;
-        return (E[0] == 1 ? 1 : g) * (E[1] == 1 ? 1 : g) * (E[2] == 1 ? 1 : g);
-    };
     const double scale = st->tune_scale;
     uint64_t acc[kCands];
+#pragma unroll
     for (int c = 0; c < kCands; c++)
         acc[c] = 0;
-    if (part == 0) {
-        tune_level(blk, E, 8, 0, targets(8), scale, acc);
-        tune_flush(st, 0, acc, red);
-        tune_level(blk, E, 4, 0, targets(4), scale, acc);
-        tune_flush(st, 1, acc, red);
-    } else if (part <= 2) {
-        const int G3 = targets(2), h = part - 1;
-        tune_level(blk, E, 2, h * G3 / 2, (h + 1) * G3 / 2, scale, acc);
-        tune_flush(st, 2, acc, red);
-    } else {
-        const int G3 = targets(1), h = part - 3;
-        tune_level(blk, E, 1, h * G3 / 6, (h + 1) * G3 / 6, scale, acc);
-        tune_flush(st, 3, acc, red);
+    // stride 8 and 4 in one part, stride 2 in two, stride 1 in six
+    const int l0 = part == 0 ? 0 : (part <= 2 ? 2 : 3), l1 = part == 0 ? 1 : l0;
+#pragma unroll 1
+    for (int l = l0; l <= l1; l++) {
+        if (part == 0)
+            tune_level(blk, E, 8 >> l, 0, 1, scale, acc);
+        else
+            tune_level(blk, E, 8 >> l, part <= 2 ? part - 1 : part - 3, part <= 2 ? 2 : 6, scale, acc);
+        tune_flush(st, l, acc, red);
     }
 }
 
