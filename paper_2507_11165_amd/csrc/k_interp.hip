@@ -1157,7 +1157,9 @@ __global__ __launch_bounds__((Tile<TZ, NX>::NT), 4) void k_predict(const Job *__
     __shared__ __align__(16) float v[T::NV];
     __shared__ __align__(4) uint8_t lc[T::OX * 8 * T::KZ];
     // a tile's histogram: two 16-bit counts per word (a tile holds at most
-    // 16384 codes), taken over into registers after each tile
+    // 16384 codes), taken over into registers after each tile. Code k shares a
+    // word with k + 128, so that the frequent codes around 128 lie in words of
+    // their own (k beside k + 1: 1800 x 3600 203 us instead of 117).
     __shared__ uint32_t hist[128];
     __shared__ uint32_t red[2 * T::NW < 8 ? 8 : 2 * T::NW];
     constexpr int HW = T::NT >= 128 ? 1 : 2; // histogram words per thread
@@ -1187,12 +1189,12 @@ __global__ __launch_bounds__((Tile<TZ, NX>::NT), 4) void k_predict(const Job *__
 #pragma unroll
             for (int b = 0; b < 2; b++) {
                 if (cnt[k][b])
-                    atomicAdd(&h[2 * (t + k * T::NT) + b], (unsigned long long)cnt[k][b]);
+                    atomicAdd(&h[t + k * T::NT + 128 * b], (unsigned long long)cnt[k][b]);
                 cnt[k][b] = 0;
             }
     };
     auto count = [&](uint32_t code) __attribute__((always_inline)) {
-        atomicAdd(&hist[code >> 1], 1u << (16 * (code & 1)));
+        atomicAdd(&hist[code & 127], 1u << (16 * (code >> 7)));
     };
     const PlaceBits<TZ, NX> P0(t);
     TileWalk w = tile_walk(lo, hi);
