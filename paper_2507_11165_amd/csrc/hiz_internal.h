@@ -82,7 +82,7 @@ struct FieldState {
     float eps, two_eb;
     // ---- device-only ----
     float inv;
-    uint32_t pad1;
+    uint32_t tuned;      // workgroups of the tuner that are done
     double tune_scale;
     uint8_t cfg[kLevels][3];
     uint8_t pad2[4];
@@ -109,7 +109,7 @@ struct Job {
     uint64_t *lb_b;      // look-back status words (encoder groups: outliers)
     uint64_t *woff;      // encoder: payload word offset of each chunk
     uint64_t *zoff;      // encoder: first outlier slot of each chunk
-    uint2 *mm_part;      // per-unit (min, max) key partials: minmax units (REL) or tiles (ABS)
+    uint2 *mm_part;      // (min, max) key partials: of the min/max workgroups (REL) or tiles (ABS)
     uint64_t dims[3];
     uint64_t N;
     uint32_t nb[3];      // blocks per axis = ceil(d / 16)
@@ -174,12 +174,14 @@ struct Counters {
 enum WorkKind { WK_MM, WK_TUNE, WK_TILE, WK_CHUNK, WK_GROUP, WK_DBLK, WK_OUT, WK_LC, WK_OU };
 constexpr int kEncGroupChunks = 64; // chunks per workgroup of the encoder's sizing pass
 
-void launch_init_compress(const Job *d_jobs, int njobs, uint64_t max_chunks, Counters *cnt,
-                          hipStream_t s);
-void launch_minmax(const Job *d_jobs, int njobs, uint64_t total, int grid, hipStream_t s);
-void launch_eps(const Job *d_jobs, int njobs, hipStream_t s);
-void launch_tune(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s);
-void launch_tune_pick(const Job *d_jobs, int njobs, hipStream_t s);
+// h_jobs: the Job table in pinned host memory, copied to d_jobs
+void launch_init_compress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_chunks,
+                          Counters *cnt, hipStream_t s);
+// mm_grid: workgroups of the min/max launch, which bound its partials per field.
+uint32_t minmax_grid(uint64_t total, int cus);
+void launch_minmax(const Job *d_jobs, int njobs, uint64_t total, uint32_t mm_grid, hipStream_t s);
+void launch_eps(const Job *d_jobs, int njobs, uint32_t mm_grid, hipStream_t s);
+void launch_tune(const Job *d_jobs, int njobs, uint64_t total, uint32_t mm_grid, hipStream_t s);
 // The tile kernels run over the tiles [lo, hi) of the work list, which belong
 // to the njobs jobs at d_jobs (all of one tile kind).
 void launch_predict(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int kind, int grid,
@@ -191,9 +193,9 @@ void launch_encode(const Job *d_jobs, int njobs, uint64_t total_chunks, uint64_t
 int encode_blocks_per_cu();
 
 void launch_fill(float *out, uint64_t n, float v, hipStream_t s);
-void launch_gather_results(const Job *d_jobs, int njobs, void *d_dst, hipStream_t s);
-void launch_init_decompress(const Job *d_jobs, int njobs, uint64_t max_blocks, Counters *cnt,
-                            hipStream_t s);
+void launch_gather_results(const Job *d_jobs, int njobs, void *h_dst, hipStream_t s);
+void launch_init_decompress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_blocks,
+                            Counters *cnt, hipStream_t s);
 void launch_dec_tables(const Job *d_jobs, int njobs, uint64_t max_blocks, hipStream_t s);
 // The decoder's work units are sub-blocks of kDecSub chunks, an even number
 // per field, so that a workgroup of 2 * kDecSub lanes can take a pair of one
@@ -322,6 +324,21 @@ __device__ inline int find_job(const Job *jobs, int njobs, uint64_t u)
     return lo;
 }
 
+// Job blockIdx.y into LDS for the whole workgroup; the first workgroup of each
+// job also copies it to the device's table.
+__device__ inline void copy_job(Job &J, const Job *h_jobs, Job *d_jobs)
+{
+    constexpr int W = (int)(sizeof(Job) / 8);
+    static_assert(sizeof(Job) % 8 == 0 && W <= 256, "a Job as 8-byte words, one per thread");
+    if (threadIdx.x < W) {
+        const uint64_t v = reinterpret_cast<const uint64_t *>(h_jobs + blockIdx.y)[threadIdx.x];
+        reinterpret_cast<uint64_t *>(&J)[threadIdx.x] = v;
+        if (blockIdx.x == 0)
+            reinterpret_cast<uint64_t *>(d_jobs + blockIdx.y)[threadIdx.x] = v;
+    }
+    __syncthreads();
+}
+
 // Min/max of ordered keys over a workgroup of 256 threads; result in lane 0
 // of wave 0 (other threads get partial values). `red` is 8 words of LDS.
 __device__ inline void block_minmax(uint32_t &kmn, uint32_t &kmx, uint32_t *red)
@@ -377,6 +394,9 @@ __device__ inline void reduce_partials(const uint2 *p, uint64_t n, uint32_t &kmn
 // by an atomic counter, so every predecessor is already running.
 // ---------------------------------------------------------------------------
 constexpr uint64_t LB_AGG = 1ull << 62, LB_INC = 2ull << 62, LB_MASK = (1ull << 62) - 1;
+
+// Waits for all of the wave's own memory operations, atomics included.
+__device__ inline void drain_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
 __device__ inline uint64_t lb_load(const uint64_t *p)
 {

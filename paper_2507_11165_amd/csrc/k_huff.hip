@@ -751,10 +751,11 @@ int encode_blocks_per_cu()
 // ---------------------------------------------------------------------------
 // Decompression
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_init_decompress(const Job *__restrict__ jobs, int njobs,
-                                                         Counters *cnt)
+__global__ __launch_bounds__(256) void k_init_decompress(const Job *__restrict__ h_jobs,
+                                                         Job *__restrict__ d_jobs, Counters *cnt)
 {
-    const Job &J = jobs[blockIdx.y];
+    __shared__ Job J;
+    copy_job(J, h_jobs, d_jobs);
     const uint32_t t = threadIdx.x;
     if (blockIdx.x == 0) {
         if (t == 0) {
@@ -775,16 +776,16 @@ __global__ __launch_bounds__(256) void k_init_decompress(const Job *__restrict__
         J.lb_c[i] = 0;
 }
 
-void launch_init_decompress(const Job *d_jobs, int njobs, uint64_t max_blocks, Counters *cnt,
-                            hipStream_t s)
+void launch_init_decompress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_blocks,
+                            Counters *cnt, hipStream_t s)
 {
     uint64_t gx = cdiv(max_blocks, 256);
     if (gx < 1)
         gx = 1;
     if (gx > 1024)
         gx = 1024;
-    hipLaunchKernelGGL(k_init_decompress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, d_jobs,
-                       njobs, cnt);
+    hipLaunchKernelGGL(k_init_decompress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, h_jobs,
+                       d_jobs, cnt);
 }
 
 // Decoder tables from the stored code lengths: canonical codes, a direct

@@ -8,13 +8,66 @@
 namespace hiz {
 
 // ---------------------------------------------------------------------------
-// Reset of per-field state and look-back flags (a fill kernel rather than
-// hipMemsetAsync so that the sequence can be captured in a HIP graph).
+// Error bound: eps = eb (ABS) or eb * (max - min) (REL), formed in FP64 and
+// rounded down to FP32 so that it never exceeds the requested bound.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ jobs, int njobs,
-                                                       Counters *cnt)
+__device__ inline float bound_of(double e)
 {
-    const Job &J = jobs[blockIdx.y];
+    float f = (float)e;
+    if ((double)f > e)
+        f = nextafterf(f, 0.0f);
+    return f;
+}
+__device__ inline double tune_scale_of(float f)
+{
+    return f > 0.0f ? 65536.0 / (2.0 * (double)f) : 65536.0;
+}
+__device__ inline void store_bound(FieldState *st, double e)
+{
+    const float f = bound_of(e);
+    st->eps = f;
+    st->two_eb = f * 2.0f;
+    st->inv = 1.0f / st->two_eb;
+    st->tune_scale = tune_scale_of(f);
+}
+// REL, behind the launch that found the extremes: the bound in FP64. False: the
+// field is constant.
+__device__ inline bool rel_bound(const Job &J, uint32_t kmn, uint32_t kmx, double &e)
+{
+    const double range = (double)fkey_inv(kmx) - (double)fkey_inv(kmn);
+    e = J.eb * range;
+    return range != 0.0;
+}
+__device__ inline void store_rel_bound(const Job &J, FieldState *st, uint32_t kmn, uint32_t kmx)
+{
+    st->kmin = kmn;
+    st->kmax = kmx;
+    st->vmin = fkey_inv(kmn);
+    st->vmax = fkey_inv(kmx);
+    double e;
+    if (rel_bound(J, kmn, kmx, e))
+        store_bound(st, e);
+    else
+        atomicOr(&st->flags, (uint32_t)ST_CONST);
+}
+__device__ inline void store_cfg(FieldState *st, int l, int sp, int sc, int pm)
+{
+    st->cfg[l][0] = (uint8_t)sp;
+    st->cfg[l][1] = (uint8_t)sc;
+    st->cfg[l][2] = (uint8_t)pm;
+}
+
+// ---------------------------------------------------------------------------
+// Reset of per-field state and look-back flags (a fill kernel rather than
+// hipMemsetAsync so that the sequence can be captured in a HIP graph). The Job
+// table is read from pinned host memory and copied to the device on the way,
+// which saves the call a copy of its own (each one some 5 us on the stream).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ h_jobs,
+                                                       Job *__restrict__ d_jobs, Counters *cnt)
+{
+    __shared__ Job J;
+    copy_job(J, h_jobs, d_jobs);
     FieldState *st = J.st;
     const uint32_t t = threadIdx.x;
     if (blockIdx.x == 0) {
@@ -27,6 +80,20 @@ __global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ j
             st->payload_words = 0;
             st->total_bytes = 0;
             st->zeros_seen = 0;
+            st->tuned = 0;
+            if (J.mode != 1)
+                store_bound(st, J.eb);
+        }
+        // without a sample to measure: the configuration asked for, or the
+        // default one; with one, what a constant field's header records
+        if (t < kLevels) {
+            const uint8_t *cf = J.cfg_forced[t];
+            if (J.n_tune != 0)
+                store_cfg(st, t, 0, 0, 0);
+            else if (J.tune)
+                store_cfg(st, t, 1, 0, 0);
+            else
+                store_cfg(st, t, cf[0], cf[1], cf[2]);
         }
         if (blockIdx.y == 0 && t < sizeof(Counters) / 4)
             reinterpret_cast<uint32_t *>(cnt)[t] = 0u;
@@ -43,21 +110,25 @@ __global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ j
         J.lb_d[i] = 0;
 }
 
-void launch_init_compress(const Job *d_jobs, int njobs, uint64_t max_chunks, Counters *cnt,
-                          hipStream_t s)
+void launch_init_compress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_chunks,
+                          Counters *cnt, hipStream_t s)
 {
     uint64_t gx = cdiv(max_chunks, 256);
     if (gx < 1)
         gx = 1;
     if (gx > 1024)
         gx = 1024;
-    hipLaunchKernelGGL(k_init_compress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, d_jobs, njobs,
+    hipLaunchKernelGGL(k_init_compress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, h_jobs, d_jobs,
                        cnt);
 }
 
 // ---------------------------------------------------------------------------
-// Exact min/max (REL mode): ordered 32-bit keys reduced with atomics, so the
-// result does not depend on the order of reduction; NaN/Inf raise a flag.
+// Exact min/max (REL mode): ordered 32-bit keys, so the result does not depend
+// on the order of reduction; NaN/Inf raise a flag. A workgroup keeps its extremes
+// over all its units of a field and stores them in the slot of the first of
+// them, which is below the grid's size: a field has min(units, grid) slots, and
+// whoever needs the bound reduces those. (Atomics on two words of the field
+// instead: 100 x 500 x 500 59 us, this way 29.)
 // ---------------------------------------------------------------------------
 
 __device__ inline uint32_t wave_min_u32(uint32_t v)
@@ -78,14 +149,34 @@ __global__ __launch_bounds__(256) void k_minmax(const Job *__restrict__ jobs, in
 {
     __shared__ uint32_t red[8];
     const uint32_t t = threadIdx.x;
+    int cur = -1;
+    uint64_t slot = 0;
+    uint32_t kmn = 0xffffffffu, kmx = 0u;
+    bool bad = false;
+    auto flush = [&]() {
+        if (__any(bad) && (t & 63) == 0)
+            atomicOr(&jobs[cur].st->flags, (uint32_t)ST_NONFINITE);
+        block_minmax(kmn, kmx, red);
+        if (t == 0)
+            gstore_u2(gmem(jobs[cur].mm_part) + slot, make_uint2(kmn, kmx));
+        kmn = 0xffffffffu;
+        kmx = 0u;
+        bad = false;
+        __syncthreads(); // red is free again
+    };
     for (uint64_t u = blockIdx.x; u < total; u += gridDim.x) {
-        const Job &J = jobs[find_job<WK_MM>(jobs, njobs, u)];
+        const int ji = find_job<WK_MM>(jobs, njobs, u);
+        if (ji != cur) {
+            if (cur >= 0)
+                flush();
+            cur = ji;
+            slot = u - jobs[ji].mm_begin;
+        }
+        const Job &J = jobs[ji];
         const uint64_t lu = u - J.mm_begin;
         const uint64_t lo = lu * kMmUnit;
         const uint64_t hi = min(lo + kMmUnit, J.N);
         HIZ_GLOBAL const float *f = gmem(J.field);
-        uint32_t kmn = 0xffffffffu, kmx = 0u;
-        bool bad = false;
         const bool vec = ((reinterpret_cast<uintptr_t>(f) & 15u) == 0) && (hi - lo == kMmUnit);
         if (vec) {
             // all 16 loads of a thread in flight before any is used: one
@@ -118,65 +209,40 @@ __global__ __launch_bounds__(256) void k_minmax(const Job *__restrict__ jobs, in
                 kmx = max(kmx, key);
             }
         }
-        if (__any(bad) && (t & 63) == 0)
-            atomicOr(&J.st->flags, (uint32_t)ST_NONFINITE);
-        block_minmax(kmn, kmx, red);
-        if (t == 0)
-            gstore_u2(gmem(J.mm_part) + lu, make_uint2(kmn, kmx));
     }
+    if (cur >= 0)
+        flush();
 }
 
-void launch_minmax(const Job *d_jobs, int njobs, uint64_t total, int grid, hipStream_t s)
+uint32_t minmax_grid(uint64_t total, int cus)
+{
+    return (uint32_t)(total < 8ull * cus ? total : 8ull * cus);
+}
+
+void launch_minmax(const Job *d_jobs, int njobs, uint64_t total, uint32_t grid, hipStream_t s)
 {
     if (total == 0)
         return;
-    uint64_t g = total < (uint64_t)grid ? total : (uint64_t)grid;
-    hipLaunchKernelGGL(k_minmax, dim3((uint32_t)g), dim3(256), 0, s, d_jobs, njobs, total);
+    hipLaunchKernelGGL(k_minmax, dim3(grid), dim3(256), 0, s, d_jobs, njobs, total);
 }
 
-// ---------------------------------------------------------------------------
-// Error bound: eps = eb (ABS) or eb * (max - min) (REL), formed in FP64 and
-// rounded down to FP32 so that it never exceeds the requested bound.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_eps(const Job *__restrict__ jobs, int njobs)
+// The bound of REL fields whose configuration is not measured (the tuner's
+// launch forms it for the others).
+__global__ __launch_bounds__(256) void k_eps(const Job *__restrict__ jobs, uint32_t mm_grid)
 {
     __shared__ uint32_t red[8];
     const Job &J = jobs[blockIdx.x];
-    FieldState *st = J.st;
-    double e = J.eb;
-    if (J.mode == 1) {
-        uint32_t kmn, kmx;
-        reduce_partials(J.mm_part, J.n_mm, kmn, kmx, red);
-        if (threadIdx.x != 0)
-            return;
-        st->kmin = kmn;
-        st->kmax = kmx;
-        if (st->flags & ST_NONFINITE)
-            return;
-        const float vmin = fkey_inv(kmn), vmax = fkey_inv(kmx);
-        st->vmin = vmin;
-        st->vmax = vmax;
-        const double range = (double)vmax - (double)vmin;
-        if (range == 0.0) {
-            st->flags |= ST_CONST;
-            return;
-        }
-        e = J.eb * range;
-    } else if (threadIdx.x != 0) {
+    if (J.mode != 1 || J.n_tune != 0 || (J.st->flags & ST_NONFINITE))
         return;
-    }
-    float f = (float)e;
-    if ((double)f > e)
-        f = nextafterf(f, 0.0f);
-    st->eps = f;
-    st->two_eb = f * 2.0f;
-    st->inv = 1.0f / st->two_eb;
-    st->tune_scale = f > 0.0f ? 65536.0 / (2.0 * (double)f) : 65536.0;
+    uint32_t kmn, kmx;
+    reduce_partials(J.mm_part, min(J.n_mm, (uint64_t)mm_grid), kmn, kmx, red);
+    if (threadIdx.x == 0)
+        store_rel_bound(J, J.st, kmn, kmx);
 }
 
-void launch_eps(const Job *d_jobs, int njobs, hipStream_t s)
+void launch_eps(const Job *d_jobs, int njobs, uint32_t mm_grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_eps, dim3(njobs), dim3(256), 0, s, d_jobs, njobs);
+    hipLaunchKernelGGL(k_eps, dim3(njobs), dim3(256), 0, s, d_jobs, mm_grid);
 }
 
 // ---------------------------------------------------------------------------
@@ -380,8 +446,37 @@ __device__ void tune_flush(FieldState *st, int level, uint64_t acc[kCands], uint
     __syncthreads();
 }
 
+// Per-level argmin by one wave: each lane holds one candidate's error of every
+// level, and a wave argmin takes the smallest, the lower candidate on equal
+// errors (the first in candidate order).
+__device__ void pick(FieldState *st)
+{
+    static_assert(kCands <= 64, "one lane per candidate");
+    const int lane = threadIdx.x & 63;
+    uint64_t err[kLevels];
+#pragma unroll
+    for (int l = 0; l < kLevels; l++)
+        err[l] = lane < kCands ? lb_load(&st->tune_err[l][lane]) : ~0ull;
+#pragma unroll
+    for (int l = 0; l < kLevels; l++) {
+        uint64_t e = err[l];
+        int c = lane;
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t e2 = shfl64(e, lane ^ o);
+            const int c2 = __shfl_xor(c, o, 64);
+            if (e2 < e || (e2 == e && c2 < c)) {
+                e = e2;
+                c = c2;
+            }
+        }
+        const int r = c % 7;
+        if (lane == 0)
+            store_cfg(st, l, c / 7, r == 0 ? 0 : 1, r == 0 ? 0 : r - 1);
+    }
+}
+
 __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int njobs,
-                                              uint64_t total)
+                                              uint64_t total, uint32_t mm_grid)
 {
     __shared__ float blk[kSide * kSide * kSide];
     __shared__ uint64_t red[4 * kCands];
@@ -390,7 +485,7 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
         return;
     const Job &J = jobs[find_job<WK_TUNE>(jobs, njobs, u)];
     FieldState *st = J.st;
-    if (st->flags & (ST_CONST | ST_NONFINITE))
+    if (st->flags & ST_NONFINITE)
         return;
     const uint64_t lu = u - J.tune_begin;
     const uint64_t j = lu / kTuneParts;
@@ -415,6 +510,26 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
         const bool in = x < E[0] && y < E[1] && z < E[2]; // (past the block's last point: x = 17)
         e[k] = f0[in ? (x * dy + y) * dz + z : 0];
     }
+    // a REL field's bound: every workgroup forms it, the first one stores it
+    double scale;
+    if (J.mode == 1) {
+        uint32_t *red32 = reinterpret_cast<uint32_t *>(red);
+        uint32_t kmn, kmx;
+        reduce_partials(J.mm_part, min(J.n_mm, (uint64_t)mm_grid), kmn, kmx, red32);
+        if (threadIdx.x == 0) {
+            red32[0] = kmn;
+            red32[1] = kmx;
+            if (lu == 0)
+                store_rel_bound(J, st, kmn, kmx);
+        }
+        __syncthreads();
+        double b;
+        if (!rel_bound(J, red32[0], red32[1], b))
+            return;
+        scale = tune_scale_of(bound_of(b));
+    } else {
+        scale = st->tune_scale;
+    }
 #pragma unroll
     for (int k = 0; k < IB; k++) {
         const int i = threadIdx.x + 256 * k;
@@ -422,7 +537,6 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
             blk[i] = e[k];
     }
     __syncthreads();
-    const double scale = st->tune_scale;
     uint64_t acc[kCands];
 #pragma unroll
     for (int c = 0; c < kCands; c++)
@@ -437,69 +551,25 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
             tune_level(blk, E, 8 >> l, part <= 2 ? part - 1 : part - 3, part <= 2 ? 2 : 6, scale, acc);
         tune_flush(st, l, acc, red);
     }
+    // The field's last workgroup picks: every workgroup's sums are in place
+    // (its wave 0 has waited for its atomics) before it counts itself.
+    if (threadIdx.x >= 64)
+        return;
+    drain_memory();
+    int last = 0;
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(&st->tuned, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+               (uint32_t)J.n_tune - 1;
+    if (__builtin_amdgcn_readfirstlane(last))
+        pick(st);
 }
 
-void launch_tune(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s)
+void launch_tune(const Job *d_jobs, int njobs, uint64_t total, uint32_t mm_grid, hipStream_t s)
 {
     if (total == 0)
         return;
-    hipLaunchKernelGGL(k_tune, dim3((uint32_t)total), dim3(256), 0, s, d_jobs, njobs, total);
-}
-
-// Per-level argmin (ties to the lower candidate), or the forced/default
-// configuration when the tuner is off or no full block exists.
-// One wave per field: each lane loads one candidate's error of every level at
-// once, and a wave argmin picks the smallest error, the lower candidate on
-// equal errors (the first in candidate order).
-__global__ __launch_bounds__(64) void k_tune_pick(const Job *__restrict__ jobs, int njobs)
-{
-    static_assert(kCands <= 64, "one lane per candidate");
-    const Job &J = jobs[blockIdx.x];
-    FieldState *st = J.st;
-    const int lane = threadIdx.x;
-    const bool measured = J.tune && J.n_samples > 0;
-    uint64_t err[kLevels];
-#pragma unroll
-    for (int l = 0; l < kLevels; l++)
-        err[l] = measured && lane < kCands ? st->tune_err[l][lane] : ~0ull;
-#pragma unroll
-    for (int l = 0; l < kLevels; l++) {
-        uint64_t e = err[l];
-        int c = lane;
-        for (int o = 32; o > 0; o >>= 1) {
-            const uint64_t e2 = shfl64(e, lane ^ o);
-            const int c2 = __shfl_xor(c, o, 64);
-            if (e2 < e || (e2 == e && c2 < c)) {
-                e = e2;
-                c = c2;
-            }
-        }
-        if (lane != 0)
-            continue;
-        uint8_t sp, sc, pm;
-        if (measured) {
-            const int r = c % 7;
-            sp = (uint8_t)(c / 7);
-            sc = (uint8_t)(r == 0 ? 0 : 1);
-            pm = (uint8_t)(r == 0 ? 0 : r - 1);
-        } else if (J.tune) {
-            sp = 1;
-            sc = 0;
-            pm = 0;
-        } else {
-            sp = J.cfg_forced[l][0];
-            sc = J.cfg_forced[l][1];
-            pm = J.cfg_forced[l][2];
-        }
-        st->cfg[l][0] = sp;
-        st->cfg[l][1] = sc;
-        st->cfg[l][2] = pm;
-    }
-}
-
-void launch_tune_pick(const Job *d_jobs, int njobs, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_tune_pick, dim3(njobs), dim3(64), 0, s, d_jobs, njobs);
+    hipLaunchKernelGGL(k_tune, dim3((uint32_t)total), dim3(256), 0, s, d_jobs, njobs, total,
+                       mm_grid);
 }
 
 // ---------------------------------------------------------------------------
@@ -522,7 +592,7 @@ void launch_fill(float *out, uint64_t n, float v, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------
-// The first bytes of every job's state, packed for one device-to-host copy.
+// The first bytes of every job's state, written to pinned host memory.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_gather_results(const Job *__restrict__ jobs, int njobs,
                                                         uint32_t *__restrict__ dst)
@@ -535,11 +605,11 @@ __global__ __launch_bounds__(256) void k_gather_results(const Job *__restrict__ 
     dst[i] = reinterpret_cast<const uint32_t *>(jobs[j].st)[w];
 }
 
-void launch_gather_results(const Job *d_jobs, int njobs, void *d_dst, hipStream_t s)
+void launch_gather_results(const Job *d_jobs, int njobs, void *h_dst, hipStream_t s)
 {
     const uint64_t n = (uint64_t)njobs * (kResultBytes / 4);
     hipLaunchKernelGGL(k_gather_results, dim3((uint32_t)cdiv(n, 256)), dim3(256), 0, s, d_jobs,
-                       njobs, static_cast<uint32_t *>(d_dst));
+                       njobs, static_cast<uint32_t *>(h_dst));
 }
 
 } // namespace hiz

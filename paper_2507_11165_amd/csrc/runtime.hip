@@ -41,11 +41,11 @@ struct Pending {
 };
 
 // Launch geometry of one enqueued sequence: equal keys replay the same graph
-// (the Job table itself is re-uploaded by the graph's first node).
+// (the graph's first node takes the Job table from the pinned buffer).
 struct GraphKey {
     int kind; // 0 compress, 1 decompress
     int njobs;
-    uint64_t v[13 + 4 * kTileKinds];
+    uint64_t v[15 + 4 * kTileKinds];
     const void *ws;
     const void *pinned;
 };
@@ -730,6 +730,7 @@ struct Totals {
     uint64_t mm = 0, tune = 0, tiles = 0, chunks = 0, groups = 0, dblk = 0, out = 0;
     uint64_t max_groups = 0, max_dblk = 0;
     uint32_t max_chunk = 0;    // longest Huffman chunk
+    bool eps = false;          // some field's relative bound is formed by a launch of its own
     uint64_t lc = 0, ou = 0;   // stage chunks, outlier units
     uint64_t max_n = 0;        // largest field (reordering launch)
     bool reorder = false;      // some field's codes are reordered
@@ -745,9 +746,8 @@ struct Totals {
 struct Layout {
     Job *d_jobs;
     Counters *d_cnt;
-    uint8_t *d_res;
     uint8_t *h_res;
-    const void *h_jobs; // host copy of the Job table the sequence uploads
+    const Job *h_jobs; // Job table in pinned memory, which the sequence copies to the device
 };
 
 // Workspace sections of one field (offsets from the workspace base).
@@ -799,6 +799,7 @@ void take_sections(Arena &A, Job &J, bool decompress, Totals &T, Sections &o)
         J.group_begin = T.groups;
         T.mm += J.n_mm;
         T.tune += J.n_tune;
+        T.eps = T.eps || (J.mode == HIZ_REL && J.n_tune == 0);
         T.tiles += J.n_tiles;
         T.chunks += J.n_chunks;
         T.groups += J.n_groups;
@@ -879,7 +880,6 @@ hiz_status layout(hiz_ctx *c, std::vector<Job> &jobs, bool decompress, Totals &T
     Arena A;
     const uint64_t o_jobs = A.take(sizeof(Job) * nj);
     const uint64_t o_cnt = A.take(sizeof(Counters));
-    const uint64_t o_res = A.take((uint64_t)kResultBytes * nj);
     std::vector<Sections> o(nj);
     T = Totals();
     for (int j = 0; j < nj; j++)
@@ -900,9 +900,8 @@ hiz_status layout(hiz_ctx *c, std::vector<Job> &jobs, bool decompress, Totals &T
     memcpy(c->pinned, jobs.data(), sizeof(Job) * nj);
     L.d_jobs = reinterpret_cast<Job *>(ws + o_jobs);
     L.d_cnt = reinterpret_cast<Counters *>(ws + o_cnt);
-    L.d_res = ws + o_res;
     L.h_res = c->pinned + job_bytes;
-    L.h_jobs = c->pinned;
+    L.h_jobs = reinterpret_cast<const Job *>(c->pinned);
     return HIZ_OK;
 }
 
@@ -911,27 +910,23 @@ hiz_status layout(hiz_ctx *c, std::vector<Job> &jobs, bool decompress, Totals &T
 void enqueue_compress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipStream_t s,
                       bool prof)
 {
-    hipMemcpyAsync(L.d_jobs, L.h_jobs, sizeof(Job) * nj, hipMemcpyHostToDevice, s);
     c->chain = nullptr;
     {
         Scope sc(c, s, "init", prof, true);
-        launch_init_compress(L.d_jobs, nj, std::max(T.max_groups, T.max_clear), L.d_cnt, s);
+        launch_init_compress(L.h_jobs, L.d_jobs, nj, std::max(T.max_groups, T.max_clear), L.d_cnt, s);
     }
+    const uint32_t mm_grid = minmax_grid(T.mm, c->cus);
     if (T.mm) {
         Scope sc(c, s, "minmax", prof, true);
-        launch_minmax(L.d_jobs, nj, T.mm, c->cus * 8, s);
+        launch_minmax(L.d_jobs, nj, T.mm, mm_grid, s);
     }
-    {
+    if (T.eps) {
         Scope sc(c, s, "eps", prof, true);
-        launch_eps(L.d_jobs, nj, s);
+        launch_eps(L.d_jobs, nj, mm_grid, s);
     }
     if (T.tune) {
         Scope sc(c, s, "tune", prof, true);
-        launch_tune(L.d_jobs, nj, T.tune, s);
-    }
-    {
-        Scope sc(c, s, "tune_pick", prof, true);
-        launch_tune_pick(L.d_jobs, nj, s);
+        launch_tune(L.d_jobs, nj, T.tune, mm_grid, s);
     }
     // the tile kernels: one launch per tile kind present
     for (int k = 0; k < kTileKinds; k++) {
@@ -962,19 +957,17 @@ void enqueue_compress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipS
         launch_lc_encode(L.d_jobs, nj, T.lc, L.d_cnt, s);
     }
     c->chain = nullptr;
-    launch_gather_results(L.d_jobs, nj, L.d_res, s);
-    hipMemcpyAsync(L.h_res, L.d_res, (size_t)kResultBytes * nj, hipMemcpyDeviceToHost, s);
+    launch_gather_results(L.d_jobs, nj, L.h_res, s);
 }
 
 // The launch sequence of decompression (decode, outliers, reconstruction).
 void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipStream_t s,
                         bool prof)
 {
-    hipMemcpyAsync(L.d_jobs, L.h_jobs, sizeof(Job) * nj, hipMemcpyHostToDevice, s);
     c->chain = nullptr;
     {
         Scope sc(c, s, "init_dec", prof, true);
-        launch_init_decompress(L.d_jobs, nj, T.max_clear, L.d_cnt, s);
+        launch_init_decompress(L.h_jobs, L.d_jobs, nj, T.max_clear, L.d_cnt, s);
     }
     if (T.dblk) {
         Scope sc(c, s, "dec_tables", prof, true);
@@ -1004,8 +997,7 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
                            predict_grid(c, k, T.thi[k] - T.tlo[k], true), s);
     }
     c->chain = nullptr;
-    launch_gather_results(L.d_jobs, nj, L.d_res, s);
-    hipMemcpyAsync(L.h_res, L.d_res, (size_t)kResultBytes * nj, hipMemcpyDeviceToHost, s);
+    launch_gather_results(L.d_jobs, nj, L.h_res, s);
 }
 
 // Run the sequence eagerly, or replay (building on first use) the HIP graph of
@@ -1026,14 +1018,14 @@ hiz_status enqueue(hiz_ctx *c, int kind, const Layout &L, int nj, const Totals &
     memset(&key, 0, sizeof(key));
     key.kind = kind;
     key.njobs = nj;
-    uint64_t v[13 + 4 * kTileKinds] = {T.mm,   T.tune, T.tiles,      T.chunks,   T.groups,         T.dblk,
+    uint64_t v[15 + 4 * kTileKinds] = {T.mm,   T.tune, T.tiles,      T.chunks,   T.groups,         T.dblk,
                                        T.out,  T.max_groups, T.max_dblk, (uint64_t)c->cus, T.lc, T.ou,
-                                       T.max_chunk};
+                                       T.max_chunk, T.eps, T.reorder};
     for (int k = 0; k < kTileKinds; k++) {
-        v[13 + 4 * k] = (uint64_t)T.jlo[k];
-        v[14 + 4 * k] = (uint64_t)T.jhi[k];
-        v[15 + 4 * k] = T.tlo[k];
-        v[16 + 4 * k] = T.thi[k];
+        v[15 + 4 * k] = (uint64_t)T.jlo[k];
+        v[16 + 4 * k] = (uint64_t)T.jhi[k];
+        v[17 + 4 * k] = T.tlo[k];
+        v[18 + 4 * k] = T.thi[k];
     }
     memcpy(key.v, v, sizeof(v));
     key.ws = c->ws;
@@ -1404,7 +1396,7 @@ hiz_status compress_noalloc(hiz_ctx *c, const float *d_field, const uint64_t dim
     Arena A;
     const uint64_t o_jobs = A.take(sizeof(Job));
     const uint64_t o_cnt = A.take(sizeof(Counters));
-    const uint64_t o_res = A.take(kResultBytes);
+    A.take(kResultBytes); // not used: the limit below stays where it was
     Totals T;
     Sections o;
     take_sections(A, J, false, T, o);
@@ -1425,9 +1417,8 @@ hiz_status compress_noalloc(hiz_ctx *c, const float *d_field, const uint64_t dim
     Layout L;
     L.d_jobs = reinterpret_cast<Job *>(c->scratch + o_jobs);
     L.d_cnt = reinterpret_cast<Counters *>(c->scratch + o_cnt);
-    L.d_res = c->scratch + o_res;
     L.h_res = c->pinned + job_bytes;
-    L.h_jobs = c->pinned;
+    L.h_jobs = reinterpret_cast<const Job *>(c->pinned);
     enqueue_compress(c, L, 1, T, s, false);
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(s));
