@@ -250,6 +250,21 @@ __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ uint32_t uni32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+// A wave-uniform 64-bit value read back from the first lane, so that the
+// compiler keeps it in scalar registers. The builtin returns a signed int:
+// each half goes back to uint32_t before widening, or a low half at or above
+// 2^31 would be sign-extended over the high half.
+__device__ __forceinline__ uint64_t uni64(uint64_t u)
+{
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u);
+    return ((uint64_t)hi << 32) | lo;
+}
 __device__ __forceinline__ float4 gload_f4(HIZ_GLOBAL const float *p)
 {
     const hiz_f4v v = *(HIZ_GLOBAL const hiz_f4v *)p;
@@ -462,15 +477,20 @@ __device__ inline uint64_t lookback(uint64_t *arr, uint64_t idx, uint64_t agg)
     return excl;
 }
 
-__device__ inline uint32_t wave_incl_scan(uint32_t v)
+// Inclusive scan over the wave with DPP moves: shifts by 1, 2, 4, 8 lanes
+// within each row of 16 (zeros shifted in), then the last lane of row 0 (2)
+// added to row 1 (3), then lane 31 to rows 2 and 3. No LDS round trips.
+__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t v)
 {
-    const int lane = threadIdx.x & 63;
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t u = (uint32_t)__shfl_up((int)v, o, 64);
-        if (lane >= o)
-            v += u;
-    }
-    return v;
+    constexpr int kRowShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 2, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 4, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 8, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kBcast15, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kBcast31, 0xc, 0xf, false);
+    return (uint32_t)x;
 }
 
 __device__ inline uint64_t wave_incl_scan64(uint64_t v)

@@ -397,22 +397,6 @@ __device__ inline uint32_t zero_codes(const uint32_t r[4], int n)
     return z;
 }
 
-// Inclusive scan over the wave with DPP moves: shifts by 1, 2, 4, 8 lanes
-// within each row of 16 (zeros shifted in), then the last lane of row 0 (2)
-// added to row 1 (3), then lane 31 to rows 2 and 3. No LDS round trips.
-__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t v)
-{
-    constexpr int kRowShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
-    int x = (int)v;
-    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 1, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 2, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 4, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, kRowShr + 8, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, kBcast15, 0xa, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, kBcast31, 0xc, 0xf, false);
-    return (uint32_t)x;
-}
-
 // Bits and outliers of one lane's share of a segment.
 __device__ inline void lane_sizes(const uint32_t r[4], int n, const uint8_t *len, uint32_t &bits,
                                   uint32_t &zeros)
@@ -547,16 +531,6 @@ __global__ __launch_bounds__(256) void k_enc_sizes(const Job *__restrict__ jobs,
     }
 }
 
-// A wave-uniform 64-bit value read back from the first lane, so that the
-// compiler keeps it in scalar registers. The builtin returns a signed int:
-// each half goes back to uint32_t before widening, or a low half at or above
-// 2^31 would be sign-extended over the high half.
-__device__ __forceinline__ uint64_t uni64(uint64_t u)
-{
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u);
-    return ((uint64_t)hi << 32) | lo;
-}
 template <typename T> __device__ __forceinline__ T *uni_ptr(T *p)
 {
     return reinterpret_cast<T *>(uni64(reinterpret_cast<uint64_t>(p)));

@@ -89,10 +89,6 @@ struct Geo {
     int ownx, owny, ownz; // owned extents
 };
 
-__device__ __forceinline__ uint32_t uni32(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
 __device__ __forceinline__ float unif(float v) { return __uint_as_float(uni32(__float_as_uint(v))); }
 // The i-th of three values (passed by value: a choice between members would
 // put the struct that holds them into memory).

@@ -18,61 +18,71 @@
 //    (a bitmap of at most 8 bytes as it is; a longer one as the bitmap of its
 //    bytes that differ from the byte before, compressed the same way, then
 //    those bytes), the kept words and the bytes after the last whole word.
-// Every step is a workgroup-wide flag / scan / compaction over LDS.
+// Each stage is a pass of the workgroup over its chunk in 16-byte pieces, one
+// scan over all pieces and bitmap levels, and a compaction out of registers;
+// TCMS is done on the way in or out of its neighbour. What bounds the kernels is
+// the instructions of those passes and, per chunk, the latency of a claim, of the
+// look-back and of some five barriers; four workgroups per compute unit (36 KB
+// of LDS each) fill in for each other. 256^3: throughput mode 134 -> 35 us
+// encoding and 87 -> 39 decoding, ratio mode 108 -> 53 and 44 -> 24, the first
+// figure for loops over single bytes with a scan per bitmap level.
 #include "hiz_internal.h"
 
 namespace hiz {
 
 constexpr int kLcThreads = 256;
-constexpr int kLcBuf = kLcChunk + kLcChunk / 4 + 64; // longest stage input or output
-constexpr int kBmLevels = 6;
-constexpr int kBmBytes = 3072;                        // every bitmap level of one stage
+constexpr int kLcWaves = kLcThreads / 64;
+constexpr int kPiece = 16;                         // bytes a thread handles at a time
+constexpr int kRound = kPiece * kLcThreads;        // bytes of one round of the workgroup
+constexpr int kRounds = kLcChunk / kRound;         // rounds of a chunk
+// Longest stream between two stages: RRE_4 of a whole chunk, nothing left out
+// (2 + 512 + 64 + 8 bytes in front of the words).
+constexpr int kLcMid = kLcChunk + 2 + kLcChunk / 32 + kLcChunk / 256 + 8;
+constexpr int kMidRounds = (kLcMid + kRound - 1) / kRound;
+// Bitmap levels of up to kLcMid marks: level 0, and each level's byte marks
+// (level 3 has at most 8 bytes).
+constexpr int kBm0 = (kLcMid + 7) / 8, kBm1 = (kBm0 + 7) / 8, kBm2 = (kBm1 + 7) / 8;
+static_assert((kBm2 + 7) / 8 <= 8 && kBm1 <= 2 * kLcThreads && kBm2 <= 64, "four bitmap levels");
+constexpr int kBmOff[4] = {0, (kBm0 + 31) & ~15, ((kBm0 + 31) & ~15) + ((kBm1 + 31) & ~15),
+                           ((kBm0 + 31) & ~15) + ((kBm1 + 31) & ~15) + ((kBm2 + 31) & ~15)};
+constexpr int kBmBytes = kBmOff[3] + 16;
 
-enum : int { OP_TCMS = 0, OP_BIT = 1, OP_RRE = 2, OP_RZE = 3 };
-struct Stage {
-    int op, k;
-};
-
-template <int P> struct Pipeline;
-template <> struct Pipeline<PIPE_TP> {
-    static constexpr int n = 3;
-    __device__ static Stage at(int i)
-    {
-        return i == 0 ? Stage{OP_TCMS, 1} : i == 1 ? Stage{OP_BIT, 1} : Stage{OP_RRE, 1};
-    }
-};
-template <> struct Pipeline<PIPE_CR> {
-    static constexpr int n = 3;
-    __device__ static Stage at(int i)
-    {
-        return i == 0 ? Stage{OP_RRE, 4} : i == 1 ? Stage{OP_TCMS, 8} : Stage{OP_RZE, 1};
-    }
-};
-
+// 36 KB, so that four workgroups fit on a compute unit.
 struct LcShared {
-    alignas(16) uint8_t a[kLcBuf];
-    alignas(16) uint8_t b[kLcBuf];
+    alignas(16) uint8_t a[kLcChunk + 2 * kPiece];              // a chunk's stored form
+    alignas(16) uint8_t b[(kLcMid + 2 * kPiece) & ~15];        // between two stages
     alignas(16) uint8_t bm[kBmBytes];
-    int scan[8];
-    int flag;
+    alignas(16) uint32_t part[5][kLcWaves];
+    int pos; // decoder: bytes read so far, -1: more than there are
     uint32_t id;
     uint64_t base, zbase;
 };
+static_assert(sizeof(LcShared) <= 40960, "four workgroups per compute unit");
 
-// ---- small workgroup primitives --------------------------------------------
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u4_lds __attribute__((ext_vector_type(4)));
+
+// LDS accesses of one wave stay in this order (the LDS itself keeps it).
+__device__ __forceinline__ void wave_order() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ uint32_t pick4(const uint32_t (&w)[4], int i)
+{
+    return i == 0 ? w[0] : i == 1 ? w[1] : i == 2 ? w[2] : w[3];
+}
+
+// ---- small primitives --------------------------------------------------------
 
 // Exclusive prefix of v over the workgroup; `total` gets the sum.
 __device__ inline int wg_excl_scan(int v, int *tmp, int &total)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int incl = (int)wave_incl_scan((uint32_t)v);
+    const int incl = (int)wave_incl_scan_dpp((uint32_t)v);
     if (lane == 63)
         tmp[wv] = incl;
     __syncthreads();
     int before = 0;
     total = 0;
 #pragma unroll
-    for (int w = 0; w < kLcThreads / 64; w++) {
+    for (int w = 0; w < kLcWaves; w++) {
         const int x = tmp[w];
         before += w < wv ? x : 0;
         total += x;
@@ -81,21 +91,54 @@ __device__ inline int wg_excl_scan(int v, int *tmp, int &total)
     return before + incl - v;
 }
 
-__device__ inline uint64_t load_word(const uint8_t *p, int k)
+// N counters of at most 1024 per wave at once: `before` gets each one's
+// exclusive prefix over the workgroup, `total` its sum. One barrier; the next
+// use of `part` has to be behind another.
+template <int N>
+__device__ __forceinline__ void scan_counters(const uint32_t (&c)[N], uint32_t (&before)[N],
+                                              uint32_t (&total)[N], LcShared &S)
 {
-    uint64_t v = 0;
-    for (int b = 0; b < k; b++)
-        v |= (uint64_t)p[b] << (8 * b);
-    return v;
+    constexpr int P = (N + 1) / 2;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t in[P];
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const uint32_t v = c[2 * p] | (2 * p + 1 < N ? c[2 * p + 1] << 16 : 0u);
+        const uint32_t x = wave_incl_scan_dpp(v);
+        if (lane == 63)
+            S.part[p][wv] = x;
+        in[p] = x - v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        uint32_t b = in[p], s = 0;
+        // (a workgroup's sum of one counter is at most 4096: it fits its half)
+#pragma unroll
+        for (int w = 0; w < kLcWaves; w++) {
+            const uint32_t x = S.part[p][w];
+            b += w < wv ? x : 0u;
+            s += x;
+        }
+        before[2 * p] = b & 0xffffu;
+        total[2 * p] = s & 0xffffu;
+        if (2 * p + 1 < N) {
+            before[2 * p + 1] = b >> 16;
+            total[2 * p + 1] = s >> 16;
+        }
+    }
 }
 
-__device__ inline void store_word(uint8_t *p, int k, uint64_t v)
+// One bit per byte of x, set where the byte is not zero.
+__device__ __forceinline__ uint32_t nonzero4(uint32_t x)
 {
-    for (int b = 0; b < k; b++)
-        p[b] = (uint8_t)(v >> (8 * b));
+    const uint32_t t = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7 & 0x01010101u;
+    return t * 0x01020408u >> 24;
 }
-
-__device__ inline bool bit_of(const uint8_t *bm, int i) { return (bm[i >> 3] >> (i & 7)) & 1; }
+__device__ __forceinline__ uint32_t nonzero8(uint64_t x)
+{
+    return nonzero4((uint32_t)x) | nonzero4((uint32_t)(x >> 32)) << 4;
+}
 
 // 8x8 bit transpose: byte i of v, bit p -> byte p of the result, bit i.
 __device__ inline uint64_t transpose8(uint64_t x)
@@ -110,251 +153,531 @@ __device__ inline uint64_t transpose8(uint64_t x)
     return x;
 }
 
-// Byte sizes of the bitmap levels of m marks; returns the top level.
-__device__ inline int bitmap_levels(int m, int nb[kBmLevels], int off[kBmLevels])
+// TCMS of every byte of x, of a 64-bit word, and back.
+__device__ __forceinline__ uint32_t tcms1(uint32_t x)
 {
-    nb[0] = (m + 7) / 8;
-    off[0] = 0;
-    int L = 0;
-    while (nb[L] > 8) {
-        nb[L + 1] = (nb[L] + 7) / 8;
-        off[L + 1] = off[L] + ((nb[L] + 15) & ~15);
-        L++;
-    }
-    return L;
+    return (x << 1 & 0xfefefefeu) ^ (x >> 7 & 0x01010101u) * 255u;
+}
+__device__ __forceinline__ uint32_t tcms1_inv(uint32_t x)
+{
+    return (x >> 1 & 0x7f7f7f7fu) ^ (x & 0x01010101u) * 255u;
+}
+__device__ __forceinline__ uint64_t tcms8(uint64_t w)
+{
+    return (w << 1) ^ (uint64_t)((int64_t)w >> 63);
+}
+__device__ __forceinline__ uint64_t tcms8_inv(uint64_t w) { return (w >> 1) ^ (0ull - (w & 1)); }
+// The 64-bit words of the piece at byte i of a stream of n bytes; bytes past the
+// last whole word stay.
+template <bool INV> __device__ __forceinline__ void tcms8_piece(uint4 &x, int i, int n)
+{
+    uint64_t lo = x.x | (uint64_t)x.y << 32, hi = x.z | (uint64_t)x.w << 32;
+    if (i + 8 <= n)
+        lo = INV ? tcms8_inv(lo) : tcms8(lo);
+    if (i + 16 <= n)
+        hi = INV ? tcms8_inv(hi) : tcms8(hi);
+    x = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
-// Copy `cnt` elements of width w from src whose mark (bit i of marks) is set,
-// in order, to dst; returns how many (same value in every thread).
-__device__ int compact(const uint8_t *src, int cnt, int w, const uint8_t *marks, uint8_t *dst,
-                       int *tmp)
+// Transpose of a 4x4 byte matrix held as four words.
+__device__ __forceinline__ void transpose_bytes(uint32_t (&w)[4])
 {
-    const int per = (cnt + kLcThreads - 1) / kLcThreads;
-    const int i0 = min(cnt, (int)threadIdx.x * per), i1 = min(cnt, i0 + per);
-    int c = 0;
-    for (int i = i0; i < i1; i++)
-        c += bit_of(marks, i);
-    int total;
-    int o = wg_excl_scan(c, tmp, total);
-    for (int i = i0; i < i1; i++)
-        if (bit_of(marks, i)) {
-            for (int b = 0; b < w; b++)
-                dst[(size_t)o * w + b] = src[(size_t)i * w + b];
-            o++;
-        }
-    __syncthreads();
-    return total;
+    const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u); // w0.0 w1.0 w0.1 w1.1
+    const uint32_t b = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u); // w0.2 w1.2 w0.3 w1.3
+    const uint32_t c = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+    const uint32_t d = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    w[0] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+    w[1] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+    w[2] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+    w[3] = __builtin_amdgcn_perm(d, b, 0x07060302u);
 }
 
-// Inverse of compact: rebuild `cnt` elements of width w into dst from the
-// kept elements at src; an unmarked element repeats the previous element
-// (`fill` = 1, 0 before the first) or is zero (`fill` = 0). `avail` bounds the
-// kept elements readable at src; returns how many were read, or -1.
-__device__ int expand(const uint8_t *src, int avail, int cnt, int w, const uint8_t *marks,
-                      bool fill, uint8_t *dst, int *tmp)
-{
-    const int per = (cnt + kLcThreads - 1) / kLcThreads;
-    const int i0 = min(cnt, (int)threadIdx.x * per), i1 = min(cnt, i0 + per);
-    int c = 0;
-    for (int i = i0; i < i1; i++)
-        c += bit_of(marks, i);
-    int total;
-    int r = wg_excl_scan(c, tmp, total); // kept elements before this thread's range
-    if (total * w > avail)
-        return -1;
-    for (int i = i0; i < i1; i++) {
-        const bool m = bit_of(marks, i);
-        r += m;
-        for (int b = 0; b < w; b++)
-            dst[(size_t)i * w + b] = (m || (fill && r > 0)) ? src[(size_t)(r - 1) * w + b] : 0;
-    }
-    __syncthreads();
-    return total;
-}
-
-// ---- stages -----------------------------------------------------------------
-
-__device__ void st_tcms(const uint8_t *a, int n, int k, uint8_t *b, bool inv)
-{
-    const int m = n / k;
-    for (int i = threadIdx.x; i < m; i += kLcThreads) {
-        const uint64_t w = load_word(a + (size_t)i * k, k);
-        uint64_t r;
-        if (k == 8) {
-            r = inv ? ((w >> 1) ^ (0ull - (w & 1))) : ((w << 1) ^ (uint64_t)((int64_t)w >> 63));
-        } else {
-            const int bits = 8 * k;
-            const uint64_t mask = (1ull << bits) - 1;
-            const uint64_t sign = ((w >> (bits - 1)) & 1) ? mask : 0;
-            r = inv ? (((w >> 1) ^ ((w & 1) ? mask : 0)) & mask) : (((w << 1) & mask) ^ sign);
-        }
-        store_word(b + (size_t)i * k, k, r);
-    }
-    for (int i = m * k + threadIdx.x; i < n; i += kLcThreads)
-        b[i] = a[i];
-    __syncthreads();
-}
-
-__device__ void st_bit(const uint8_t *a, int n, uint8_t *b, bool inv)
-{
-    const int g = n / 8;
-    for (int j = threadIdx.x; j < g; j += kLcThreads) {
-        if (!inv) {
-            const uint64_t t = transpose8(load_word(a + 8 * j, 8));
+// Bytes of the bitmap levels of m marks; `top` is the last level.
+struct Bitmap {
+    int nb[4], top;
+    __device__ explicit Bitmap(int m)
+    {
+        nb[0] = (m + 7) / 8;
 #pragma unroll
-            for (int p = 0; p < 8; p++)
-                b[p * g + j] = (uint8_t)(t >> (8 * p));
-        } else {
-            uint64_t v = 0;
-#pragma unroll
-            for (int p = 0; p < 8; p++)
-                v |= (uint64_t)a[p * g + j] << (8 * p);
-            store_word(b + 8 * j, 8, transpose8(v));
-        }
+        for (int l = 1; l < 4; l++)
+            nb[l] = (nb[l - 1] + 7) / 8;
+        top = nb[0] <= 8 ? 0 : nb[1] <= 8 ? 1 : nb[2] <= 8 ? 2 : 3;
     }
-    for (int i = 8 * g + threadIdx.x; i < n; i += kLcThreads)
-        b[i] = a[i];
-    __syncthreads();
+    __device__ int top_bytes() const
+    {
+        return top == 0 ? nb[0] : top == 1 ? nb[1] : top == 2 ? nb[2] : nb[3];
+    }
+    __device__ static int top_off(int top)
+    {
+        return top == 0 ? kBmOff[0] : top == 1 ? kBmOff[1] : top == 2 ? kBmOff[2] : kBmOff[3];
+    }
+};
+// The low `n` of 8 (or more) mark bits.
+__device__ __forceinline__ uint32_t low_bits(int n) { return n >= 31 ? ~0u : (1u << max(n, 0)) - 1u; }
+
+// ---- RRE / RZE --------------------------------------------------------------
+
+// Marks of level bytes 8q..8q+7 (of n) that differ from the byte before.
+__device__ __forceinline__ uint32_t level_marks(const uint8_t *src, int q, int n)
+{
+    const uint64_t w = *reinterpret_cast<const uint64_t *>(src + 8 * q);
+    const uint64_t before = q ? src[8 * q - 1] : 0;
+    return nonzero8(w ^ (w << 8 | before)) & low_bits(n - 8 * q);
+}
+// The marked bytes of the eight at src, in order, to dst.
+__device__ __forceinline__ void keep8(uint8_t *dst, const uint8_t *src, uint32_t marks)
+{
+    const uint64_t w = *reinterpret_cast<const uint64_t *>(src);
+#pragma unroll
+    for (int k = 0; k < 8; k++)
+        if (marks >> k & 1)
+            *dst++ = (uint8_t)(w >> (8 * k));
 }
 
-// RRE_k (zero = false) / RZE_k (zero = true) of a[0..n) into b; returns the length.
-__device__ int st_reduce(const uint8_t *a, int n, int k, bool zero, uint8_t *b, LcShared &S)
+// RRE_K (ZERO = false) / RZE_K (ZERO = true) of n bytes into out, R rounds of
+// the workgroup at most. Thread t takes the 16 bytes at 4096 r + 16 t in round
+// r: fetch(r, x, before) gives them and, for RRE, the word before. What a thread
+// keeps stays in its registers until one scan over all rounds and bitmap levels
+// has told where everything goes. Returns the length; one of at least `limit`
+// is not written.
+template <int K, bool ZERO, int R, class FETCH>
+__device__ int st_reduce(FETCH fetch, int n, uint8_t *out, int limit, LcShared &S)
 {
-    const int m = n / k, tail = n - m * k;
-    int nb[kBmLevels], off[kBmLevels];
-    const int L = bitmap_levels(m, nb, off);
-    uint8_t *bm = S.bm;
-    // level 0: the word marks
-    for (int q = threadIdx.x; q < nb[0]; q += kLcThreads) {
-        uint32_t v = 0;
-        for (int i = 8 * q; i < min(m, 8 * q + 8); i++) {
-            const uint64_t w = load_word(a + (size_t)i * k, k);
-            const uint64_t before = i ? load_word(a + (size_t)(i - 1) * k, k) : 0;
-            v |= (uint32_t)(zero ? w != 0 : w != before) << (i & 7);
+    constexpr int E = kPiece / K; // words of a piece
+    const int t = threadIdx.x;
+    const int m = n / K;
+    const Bitmap B(m);
+    uint8_t *bm0 = S.bm + kBmOff[0], *bm1 = S.bm + kBmOff[1], *bm2 = S.bm + kBmOff[2],
+            *bm3 = S.bm + kBmOff[3];
+    uint4 x[R];
+    uint32_t marks[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = kRound * r + kPiece * t;
+        marks[r] = 0;
+        if (i < n) {
+            uint32_t before = 0;
+            fetch(r, x[r], before);
+            const uint4 v = x[r];
+            if (K == 4) {
+                marks[r] = (uint32_t)(v.x != before) | (uint32_t)(v.y != v.x) << 1 |
+                           (uint32_t)(v.z != v.y) << 2 | (uint32_t)(v.w != v.z) << 3;
+            } else if (ZERO) {
+                marks[r] = nonzero4(v.x) | nonzero4(v.y) << 4 | nonzero4(v.z) << 8 |
+                           nonzero4(v.w) << 12;
+            } else {
+                marks[r] = nonzero4(v.x ^ __builtin_amdgcn_alignbyte(v.x, before, 3)) |
+                           nonzero4(v.y ^ __builtin_amdgcn_alignbyte(v.y, v.x, 3)) << 4 |
+                           nonzero4(v.z ^ __builtin_amdgcn_alignbyte(v.z, v.y, 3)) << 8 |
+                           nonzero4(v.w ^ __builtin_amdgcn_alignbyte(v.w, v.z, 3)) << 12;
+            }
+            marks[r] &= low_bits(m - i / K);
         }
-        bm[off[0] + q] = (uint8_t)v;
+        if (K == 4) {
+            const uint32_t odd = (uint32_t)__shfl_xor((int)marks[r], 1, 64);
+            if (!(t & 1) && i < n)
+                bm0[i / 32] = (uint8_t)(marks[r] | odd << 4);
+        } else if (i < n) {
+            *reinterpret_cast<uint16_t *>(bm0 + i / 8) = (uint16_t)marks[r];
+        }
     }
     __syncthreads();
-    // level l + 1: marks of the level-l bytes that differ from the byte before
-    for (int l = 0; l < L; l++) {
-        const uint8_t *src = bm + off[l];
-        for (int q = threadIdx.x; q < nb[l + 1]; q += kLcThreads) {
-            uint32_t v = 0;
-            for (int j = 8 * q; j < min(nb[l], 8 * q + 8); j++)
-                v |= (uint32_t)(src[j] != (j ? src[j - 1] : 0)) << (j & 7);
-            bm[off[l + 1] + q] = (uint8_t)v;
+    // level 1 by the workgroup, levels 2 and 3 (34 and 5 bytes at most) by wave 0
+    uint32_t c[4 + R];
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        c[k] = 0;
+    uint32_t lm[4] = {0, 0, 0, 0}; // marks of this thread's bytes: level 2, 1, 0 and 0 again
+    if (B.top > 0) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int q = t + kLcThreads * h;
+            if (q < B.nb[1]) {
+                lm[2 + h] = level_marks(bm0, q, B.nb[0]);
+                bm1[q] = (uint8_t)lm[2 + h];
+            }
         }
         __syncthreads();
+        if (t < 64 && B.top > 1) {
+            if (t < B.nb[2]) {
+                lm[1] = level_marks(bm1, t, B.nb[1]);
+                bm2[t] = (uint8_t)lm[1];
+            }
+            wave_order();
+            if (B.top > 2 && t < B.nb[3]) {
+                lm[0] = level_marks(bm2, t, B.nb[2]);
+                bm3[t] = (uint8_t)lm[0];
+            }
+            wave_order();
+        }
     }
-    if (threadIdx.x == 0) {
-        b[0] = (uint8_t)(n & 255);
-        b[1] = (uint8_t)(n >> 8);
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        c[k] = __popc(lm[k]);
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        c[4 + r] = __popc(marks[r]);
+    uint32_t o[4 + R], total[4 + R];
+    scan_counters<4 + R>(c, o, total, S);
+    const int nt = B.top_bytes();
+    int len = 2 + nt;
+#pragma unroll
+    for (int k = 0; k < 4 + R; k++) {
+        const int w = k < 4 ? 1 : K;
+        o[k] = (uint32_t)len + w * o[k];
+        len += w * (int)total[k];
     }
-    int o = 2;
-    for (int j = threadIdx.x; j < nb[L]; j += kLcThreads)
-        b[o + j] = bm[off[L] + j];
-    o += nb[L];
+    const int tail = n - m * K;
+    if (len + tail >= limit)
+        return len + tail;
+    if (t < 64) {
+        if (t == 0) {
+            out[0] = (uint8_t)(n & 255);
+            out[1] = (uint8_t)(n >> 8);
+        }
+        if (t < nt)
+            out[2 + t] = S.bm[Bitmap::top_off(B.top) + t];
+        if (lm[0])
+            keep8(out + o[0], bm2 + 8 * t, lm[0]);
+        if (lm[1])
+            keep8(out + o[1], bm1 + 8 * t, lm[1]);
+    }
+    if (lm[2])
+        keep8(out + o[2], bm0 + 8 * t, lm[2]);
+    if (lm[3])
+        keep8(out + o[3], bm0 + 8 * (t + kLcThreads), lm[3]);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const uint32_t w[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+        uint8_t *p = out + o[4 + r];
+#pragma unroll
+        for (int k = 0; k < E; k++)
+            if (marks[r] >> k & 1) {
+                if (K == 4) {
+#pragma unroll
+                    for (int b = 0; b < 4; b++)
+                        p[b] = (uint8_t)(w[k] >> (8 * b));
+                } else {
+                    *p = (uint8_t)(w[k / 4] >> (8 * (k & 3)));
+                }
+                p += K;
+            }
+        // bytes past the last whole word
+        if (K > 1) {
+            const int i = kRound * r + kPiece * t, e = m * K - i;
+            if (tail && e >= 0 && e < kPiece)
+                for (int b = 0; b < tail; b++)
+                    out[len + b] = (uint8_t)(pick4(w, e / 4) >> (8 * b));
+        }
+    }
     __syncthreads();
-    for (int l = L - 1; l >= 0; l--)
-        o += compact(bm + off[l], nb[l], 1, bm + off[l + 1], b + o, S.scan);
-    o += k * compact(a, m, k, bm + off[0], b + o, S.scan);
-    for (int i = threadIdx.x; i < tail; i += kLcThreads)
-        b[o + i] = a[(size_t)m * k + i];
-    __syncthreads();
-    return o + tail;
+    return len + tail;
 }
 
-// Inverse of st_reduce on a[0..avail); returns the restored length or -1.
-__device__ int st_reduce_inv(const uint8_t *a, int avail, int k, bool zero, uint8_t *b,
-                             LcShared &S)
+// Eight level bytes from their marks: kept bytes at src, `r` of them before.
+__device__ __forceinline__ uint64_t spread8(const uint8_t *src, uint32_t r, uint32_t marks)
 {
+    uint64_t v = 0;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        r += marks >> k & 1;
+        const uint32_t e = src[(int)r - 1]; // (with r = 0 a byte of the length or a bitmap)
+        v |= (uint64_t)(r ? e : 0u) << (8 * k);
+    }
+    return v;
+}
+// A bitmap level of at most 512 bytes from the marks of the level above, by one
+// wave; false: fewer than the marked bytes are left at pos.
+__device__ __forceinline__ bool restore_level(const uint8_t *a, int avail, int &pos,
+                                              const uint8_t *marks, uint8_t *dst, int n)
+{
+    const int t = threadIdx.x & 63;
+    const uint32_t mk = 8 * t < n ? marks[t] & low_bits(n - 8 * t) : 0u;
+    const uint32_t c = __popc(mk), incl = wave_incl_scan_dpp(c);
+    const int total = __builtin_amdgcn_readlane((int)incl, 63);
+    if (total > avail - pos)
+        return false;
+    if (8 * t < n)
+        *reinterpret_cast<uint64_t *>(dst + 8 * t) = spread8(a + pos, incl - c, mk);
+    pos += total;
+    return true;
+}
+
+// Inverse of st_reduce on a[0..avail): put(r, x) takes the 16 bytes at
+// 4096 r + 16 t (past the end zeros). want >= 0: the length has to be that.
+// Returns the length, or -1 with nothing put: the stream is not one of
+// st_reduce's. Every count is checked against what is left before it is read.
+template <int K, bool ZERO, int R, class PUT>
+__device__ int st_restore(const uint8_t *a, int avail, int want, PUT put, LcShared &S)
+{
+    constexpr int E = kPiece / K;
+    const int t = threadIdx.x;
     if (avail < 2)
         return -1;
-    const int n = a[0] | (a[1] << 8);
-    if (n > kLcBuf)
+    const int n = a[0] | a[1] << 8;
+    if (n > R * kRound || n > kLcMid || (want >= 0 && n != want))
         return -1;
-    const int m = n / k, tail = n - m * k;
-    int nb[kBmLevels], off[kBmLevels];
-    const int L = bitmap_levels(m, nb, off);
-    uint8_t *bm = S.bm;
-    int pos = 2;
-    if (pos + nb[L] > avail)
+    const int m = n / K, tail = n - m * K;
+    const Bitmap B(m);
+    uint8_t *bm0 = S.bm + kBmOff[0], *bm1 = S.bm + kBmOff[1], *bm2 = S.bm + kBmOff[2],
+            *bm3 = S.bm + kBmOff[3];
+    const int nt = B.top_bytes();
+    if (2 + nt > avail)
         return -1;
-    for (int j = threadIdx.x; j < nb[L]; j += kLcThreads)
-        bm[off[L] + j] = a[pos + j];
-    pos += nb[L];
-    __syncthreads();
-    for (int l = L - 1; l >= 0; l--) {
-        const int c = expand(a + pos, avail - pos, nb[l], 1, bm + off[l + 1], true, bm + off[l],
-                             S.scan);
-        if (c < 0)
-            return -1;
-        pos += c;
+    // levels above 0 by wave 0
+    if (t < 64) {
+        if (t < nt)
+            S.bm[Bitmap::top_off(B.top) + t] = a[2 + t];
+        wave_order();
+        int pos = 2 + nt;
+        bool ok = true;
+        if (B.top > 2)
+            ok = restore_level(a, avail, pos, bm3, bm2, B.nb[2]);
+        wave_order();
+        if (ok && B.top > 1)
+            ok = restore_level(a, avail, pos, bm2, bm1, B.nb[1]);
+        if (t == 0)
+            S.pos = ok ? pos : -1;
     }
-    const int c = expand(a + pos, avail - pos, m, k, bm + off[0], !zero, b, S.scan);
-    if (c < 0)
+    __syncthreads();
+    int pos = __builtin_amdgcn_readfirstlane(S.pos);
+    if (pos < 0)
         return -1;
-    pos += c * k;
-    if (pos + tail != avail)
+    if (B.top > 0) {
+        uint32_t mk[2], c[2], o[2], total[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int q = t + kLcThreads * h;
+            mk[h] = q < B.nb[1] ? bm1[q] & low_bits(B.nb[0] - 8 * q) : 0u;
+            c[h] = __popc(mk[h]);
+        }
+        scan_counters<2>(c, o, total, S);
+        if ((int)(total[0] + total[1]) > avail - pos)
+            return -1;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int q = t + kLcThreads * h;
+            if (q < B.nb[1])
+                *reinterpret_cast<uint64_t *>(bm0 + 8 * q) =
+                    spread8(a + pos, o[h] + (h ? total[0] : 0u), mk[h]);
+        }
+        pos += (int)(total[0] + total[1]);
+        __syncthreads();
+    }
+    uint32_t mk[R], c[R], o[R], total[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = kRound * r + kPiece * t;
+        mk[r] = 0;
+        if (i < n) {
+            mk[r] = K == 4 ? (uint32_t)bm0[i / 32] >> (4 * (t & 1)) & 15u
+                           : *reinterpret_cast<const uint16_t *>(bm0 + i / 8);
+            mk[r] &= low_bits(m - i / K);
+        }
+        c[r] = __popc(mk[r]);
+    }
+    scan_counters<R>(c, o, total, S);
+    int kept = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        o[r] += (uint32_t)kept;
+        kept += (int)total[r];
+    }
+    if (pos + K * kept + tail != avail)
         return -1;
-    for (int i = threadIdx.x; i < tail; i += kLcThreads)
-        b[(size_t)m * k + i] = a[pos + i];
+    const uint8_t *src = a + pos;
+    const uint32_t sh = (uint32_t)(pos & 3);
+    const uint32_t *src4 = reinterpret_cast<const uint32_t *>(src - sh);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = kRound * r + kPiece * t;
+        if (i >= n)
+            continue;
+        uint32_t w[4] = {0, 0, 0, 0};
+        int k0 = (int)o[r] - 1; // the kept word an unmarked first one repeats
+#pragma unroll
+        for (int k = 0; k < E; k++) {
+            const bool mark = mk[r] >> k & 1;
+            k0 += mark;
+            const bool has = (ZERO ? mark : k0 >= 0) && i / K + k < m;
+            const int j = has ? k0 : 0;
+            if (K == 4) {
+                const uint32_t e = __builtin_amdgcn_alignbyte(src4[j + 1], src4[j], sh);
+                w[k] = has ? e : 0u;
+            } else {
+                w[k / 4] |= (has ? (uint32_t)src[j] : 0u) << (8 * (k & 3));
+            }
+        }
+        if (K > 1) {
+            const int e = m * K - i;
+            if (tail && e >= 0 && e < kPiece)
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    if (k == e / 4)
+                        for (int b = 0; b < tail; b++)
+                            w[k] |= (uint32_t)src[K * kept + b] << (8 * b);
+        }
+        put(r, make_uint4(w[0], w[1], w[2], w[3]));
+    }
     __syncthreads();
     return n;
 }
 
-// The pipeline forward on S.a[0..n); the result is left in S.a, its length returned.
-template <int P> __device__ int pipe_forward(LcShared &S, int n)
+// ---- TCMS_1 and BIT_1 -------------------------------------------------------
+
+// TCMS_1 then BIT_1 of the n bytes at src (16-byte aligned) into b, four groups of eight bytes a
+// thread at a time: their planes' bytes are written as words. zero[r] gets a
+// bit for each zero byte of the thread's 32 in round r.
+constexpr int kBitRounds = kLcChunk / (32 * kLcThreads);
+__device__ void st_planes(HIZ_GLOBAL const uint8_t *src, int n, uint8_t *b,
+                          uint32_t (&zero)[kBitRounds])
 {
-    int len = n;
-    uint8_t *x = S.a, *y = S.b;
-    for (int i = 0; i < Pipeline<P>::n; i++) {
-        const Stage st = Pipeline<P>::at(i);
-        if (st.op == OP_TCMS)
-            st_tcms(x, len, st.k, y, false);
-        else if (st.op == OP_BIT)
-            st_bit(x, len, y, false);
-        else
-            len = st_reduce(x, len, st.k, st.op == OP_RZE, y, S);
-        uint8_t *t = x;
-        x = y;
-        y = t;
+    const int t = threadIdx.x, g = n / 8;
+    uint4 v[kBitRounds][2];
+#pragma unroll
+    for (int r = 0; r < kBitRounds; r++) {
+        const int i = 32 * (kLcThreads * r + t);
+        if (i + 32 <= n) {
+            v[r][0] = gload_u4(src + i);
+            v[r][1] = gload_u4(src + i + 16);
+        }
     }
-    if (x != S.a) {
-        for (int i = threadIdx.x; i < len; i += kLcThreads)
-            S.a[i] = x[i];
-        __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kBitRounds; r++) {
+        const int i = 32 * (kLcThreads * r + t);
+        zero[r] = 0;
+        if (i + 32 <= n) {
+            uint32_t w[8] = {v[r][0].x, v[r][0].y, v[r][0].z, v[r][0].w,
+                             v[r][1].x, v[r][1].y, v[r][1].z, v[r][1].w};
+            uint32_t lo[4], hi[4];
+#pragma unroll
+            for (int q = 0; q < 8; q++)
+                zero[r] |= (nonzero4(w[q]) ^ 15u) << (4 * q);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const uint64_t x =
+                    transpose8(tcms1(w[2 * q]) | (uint64_t)tcms1(w[2 * q + 1]) << 32);
+                lo[q] = (uint32_t)x;
+                hi[q] = (uint32_t)(x >> 32);
+            }
+            if ((g & 3) == 0) {
+                transpose_bytes(lo);
+                transpose_bytes(hi);
+#pragma unroll
+                for (int p = 0; p < 4; p++) {
+                    *reinterpret_cast<uint32_t *>(b + p * g + i / 8) = lo[p];
+                    *reinterpret_cast<uint32_t *>(b + (p + 4) * g + i / 8) = hi[p];
+                }
+            } else {
+#pragma unroll
+                for (int p = 0; p < 8; p++)
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        b[p * g + i / 8 + q] = (uint8_t)((p < 4 ? lo[q] : hi[q]) >> (8 * (p & 3)));
+            }
+        } else if (i < n) {
+            // the chunk's last bytes: whole groups, then bytes that stay
+            for (int k = 0; k < n - i; k++) {
+                const uint32_t e = src[i + k];
+                zero[r] |= (uint32_t)(e == 0) << k;
+                if (i + k >= 8 * g)
+                    b[i + k] = (uint8_t)tcms1(e);
+            }
+            for (int j = i / 8; j < g; j++) {
+                uint64_t x = 0;
+                for (int k = 0; k < 8; k++)
+                    x |= (uint64_t)(uint8_t)tcms1(src[8 * j + k]) << (8 * k);
+                x = transpose8(x);
+                for (int p = 0; p < 8; p++)
+                    b[p * g + j] = (uint8_t)(x >> (8 * p));
+            }
+        }
     }
-    return len;
+    __syncthreads();
 }
 
-// The pipeline backward on S.a[0..size); returns the restored length (the
-// result in S.a) or -1.
-template <int P> __device__ int pipe_backward(LcShared &S, int size)
+// The inverse, from b to dst (16-byte aligned); returns how many of the
+// thread's bytes are zero.
+__device__ int st_planes_inv(const uint8_t *b, int n, HIZ_GLOBAL uint8_t *dst)
 {
-    int len = size;
-    uint8_t *x = S.a, *y = S.b;
-    for (int i = Pipeline<P>::n - 1; i >= 0; i--) {
-        const Stage st = Pipeline<P>::at(i);
-        if (st.op == OP_TCMS)
-            st_tcms(x, len, st.k, y, true);
-        else if (st.op == OP_BIT)
-            st_bit(x, len, y, true);
-        else
-            len = st_reduce_inv(x, len, st.k, st.op == OP_RZE, y, S);
-        if (len < 0)
-            return -1;
-        uint8_t *t = x;
-        x = y;
-        y = t;
+    const int t = threadIdx.x, g = n / 8;
+    int zeros = 0;
+#pragma unroll
+    for (int r = 0; r < kBitRounds; r++) {
+        const int i = 32 * (kLcThreads * r + t);
+        if (i + 32 <= n) {
+            uint32_t lo[4], hi[4], w[8];
+            if ((g & 3) == 0) {
+#pragma unroll
+                for (int p = 0; p < 4; p++) {
+                    lo[p] = *reinterpret_cast<const uint32_t *>(b + p * g + i / 8);
+                    hi[p] = *reinterpret_cast<const uint32_t *>(b + (p + 4) * g + i / 8);
+                }
+                transpose_bytes(lo);
+                transpose_bytes(hi);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    lo[q] = hi[q] = 0;
+#pragma unroll
+                    for (int p = 0; p < 4; p++) {
+                        lo[q] |= (uint32_t)b[p * g + i / 8 + q] << (8 * p);
+                        hi[q] |= (uint32_t)b[(p + 4) * g + i / 8 + q] << (8 * p);
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const uint64_t x = transpose8(lo[q] | (uint64_t)hi[q] << 32);
+                w[2 * q] = tcms1_inv((uint32_t)x);
+                w[2 * q + 1] = tcms1_inv((uint32_t)(x >> 32));
+                zeros += 8 - __popc(nonzero4(w[2 * q])) - __popc(nonzero4(w[2 * q + 1]));
+            }
+            gstore_u4(dst + i, make_uint4(w[0], w[1], w[2], w[3]));
+            gstore_u4(dst + i + 16, make_uint4(w[4], w[5], w[6], w[7]));
+        } else if (i < n) {
+            for (int j = i / 8; j < g; j++) {
+                uint64_t x = 0;
+                for (int p = 0; p < 8; p++)
+                    x |= (uint64_t)b[p * g + j] << (8 * p);
+                x = transpose8(x);
+                for (int k = 0; k < 8; k++) {
+                    const uint8_t e = (uint8_t)tcms1_inv((uint32_t)(x >> (8 * k)) & 255u);
+                    zeros += e == 0;
+                    dst[8 * j + k] = e;
+                }
+            }
+            for (int k = max(i, 8 * g); k < n; k++) {
+                const uint8_t e = (uint8_t)tcms1_inv(b[k]);
+                zeros += e == 0;
+                dst[k] = e;
+            }
+        }
     }
-    if (x != S.a) {
-        for (int i = threadIdx.x; i < len; i += kLcThreads)
-            S.a[i] = x[i];
-        __syncthreads();
-    }
-    return len;
+    return zeros;
 }
+
+// n bytes from LDS (16-byte aligned) or from global memory (any alignment).
+template <class SRC> __device__ void copy_out(HIZ_GLOBAL uint8_t *dst, SRC src, int n)
+{
+    for (int i = kPiece * threadIdx.x; i < n; i += kRound) {
+        if (i + kPiece <= n)
+            *reinterpret_cast<HIZ_GLOBAL u4_any *>(dst + i) = src.piece(i);
+        else
+            for (int k = i; k < n; k++)
+                dst[k] = src.byte(k);
+    }
+}
+struct FromLds {
+    const uint8_t *p;
+    __device__ u4_any piece(int i) const { return *reinterpret_cast<const u4_lds *>(p + i); }
+    __device__ uint8_t byte(int i) const { return p[i]; }
+};
+struct FromGlobal {
+    HIZ_GLOBAL const uint8_t *p;
+    __device__ u4_any piece(int i) const { return *reinterpret_cast<HIZ_GLOBAL const u4_any *>(p + i); }
+    __device__ uint8_t byte(int i) const { return p[i]; }
+};
 
 // Stage-stream input of compression: the code sequence (throughput mode) or
 // the Huffman payload's bytes (ratio mode).
@@ -376,17 +699,30 @@ __device__ inline void lc_offsets(const Job &J, const FieldState *st, uint64_t n
     }
 }
 
+// The 16 bytes at i of n in global memory (16-byte aligned), zeros past the end.
+__device__ __forceinline__ uint4 load_piece(HIZ_GLOBAL const uint8_t *src, int i, int n)
+{
+    if (i + kPiece <= n)
+        return gload_u4(src + i);
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < kPiece; k++)
+        w[k / 4] |= (i + k < n ? (uint32_t)src[i + k] : 0u) << (8 * (k & 3));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
 // ---- compression: one workgroup per chunk -----------------------------------
 // Chunks of every job of the launch, throughput and ratio mode alike.
-__global__ __launch_bounds__(kLcThreads) void k_lc_encode(const Job *__restrict__ jobs, int njobs,
-                                                          uint64_t total, Counters *cnt)
+__global__ __launch_bounds__(kLcThreads, 4) void k_lc_encode(const Job *__restrict__ jobs,
+                                                             int njobs, uint64_t total,
+                                                             Counters *cnt)
 {
     __shared__ LcShared S;
     const int t = threadIdx.x;
     if (t == 0)
         S.id = atomicAdd(&cnt->lc_next, 1u);
     __syncthreads();
-    const uint64_t id = S.id;
+    const uint64_t id = uni32(S.id);
     if (id >= total)
         return;
     const Job &J = jobs[find_job<WK_LC>(jobs, njobs, id)];
@@ -402,62 +738,59 @@ __global__ __launch_bounds__(kLcThreads) void k_lc_encode(const Job *__restrict_
     const uint64_t lo = c * kLcChunk;
     const int n = (int)min<uint64_t>(kLcChunk, n_in - lo);
     HIZ_GLOBAL const uint8_t *src = tp ? gmem(J.seq) + lo : gmem(J.hpay) + lo;
-    // raw chunk into LDS (16-byte pieces where they fit)
-    const int n16 = n & ~15;
-    for (int i = 16 * t; i < n16; i += 16 * kLcThreads)
-        *reinterpret_cast<uint4 *>(S.a + i) = gload_u4(src + i);
-    for (int i = n16 + t; i < n; i += kLcThreads)
-        S.a[i] = src[i];
-    __syncthreads();
     // outliers of a row-major code chunk (throughput mode, codes not reordered)
     const bool outl = tp && !J.reorder;
-    int zeros = 0, zbefore = 0;
-    if (outl) {
-        const int per = kLcChunk / kLcThreads;
-        for (int i = t * per; i < min(n, (t + 1) * per); i++)
-            zeros += S.a[i] == 0;
-        int zt;
-        zbefore = wg_excl_scan(zeros, S.scan, zt);
-        if (t < 64) {
-            const uint64_t zb = lookback(J.lb_d, c, (uint64_t)zt);
-            if (t == 0)
-                S.zbase = zb;
+    uint32_t zero[kBitRounds], zbefore[kBitRounds], ztotal[kBitRounds];
+    uint32_t zt = 0;
+    int len;
+    if (tp) {
+        st_planes(src, n, S.b, zero);
+        if (outl) {
+            uint32_t zc[kBitRounds];
+#pragma unroll
+            for (int r = 0; r < kBitRounds; r++)
+                zc[r] = __popc(zero[r]);
+            static_assert(kBitRounds == 2 && 64 * 32 <= 4096, "two counters");
+            scan_counters<kBitRounds>(zc, zbefore, ztotal, S);
+            zbefore[1] += ztotal[0];
+            zt = ztotal[0] + ztotal[1];
         }
-        __syncthreads();
-        const uint64_t cap = J.cap;
-        const int ib = J.idx_bytes;
-        uint64_t z = S.zbase + zbefore;
-        HIZ_GLOBAL uint8_t *out = gmem(J.stream);
-        for (int i = t * per; i < min(n, (t + 1) * per); i++)
-            if (S.a[i] == 0) {
-                const uint64_t gi = lo + i;
-                if (st->off_oidx + (z + 1) * ib <= cap) {
-                    if (ib == 4)
-                        reinterpret_cast<HIZ_GLOBAL uint32_t *>(out + st->off_oidx)[z] = (uint32_t)gi;
-                    else
-                        reinterpret_cast<HIZ_GLOBAL uint64_t *>(out + st->off_oidx)[z] = gi;
-                }
-                if (st->off_oval + (z + 1) * 4 <= cap)
-                    reinterpret_cast<HIZ_GLOBAL float *>(out + st->off_oval)[z] = gmem(J.field)[gi];
-                z++;
-            }
-        if (c == n_lc - 1 && t == 0 && S.zbase + zt != st->n_out)
-            atomicOr(&st->flags, (uint32_t)ST_CORRUPT);
+        len = st_reduce<1, false, kRounds>(
+            [&](int r, uint4 &x, uint32_t &before) __attribute__((always_inline)) {
+                const int i = kRound * r + kPiece * t;
+                x = *reinterpret_cast<const uint4 *>(S.b + i);
+                before = i ? *reinterpret_cast<const uint32_t *>(S.b + i - 4) : 0u;
+            },
+            n, S.a, n, S);
+    } else {
+        const int n1 = st_reduce<4, false, kRounds>(
+            [&](int r, uint4 &x, uint32_t &before) __attribute__((always_inline)) {
+                const int i = kRound * r + kPiece * t;
+                x = load_piece(src, i, n);
+                before = i ? *reinterpret_cast<HIZ_GLOBAL const uint32_t *>(src + i - 4) : 0u;
+            },
+            n, S.b, kLcMid + 1, S);
+        // TCMS_8 on the way into RZE_1
+        len = st_reduce<1, true, kMidRounds>(
+            [&](int r, uint4 &x, uint32_t &) __attribute__((always_inline)) {
+                const int i = kRound * r + kPiece * t;
+                x = *reinterpret_cast<const uint4 *>(S.b + i);
+                tcms8_piece<false>(x, i, n1);
+            },
+            n1, S.a, n, S);
     }
-    int len = tp ? pipe_forward<PIPE_TP>(S, n) : pipe_forward<PIPE_CR>(S, n);
     const bool raw = len >= n;
-    if (raw) {
-        for (int i = 16 * t; i < n16; i += 16 * kLcThreads)
-            *reinterpret_cast<uint4 *>(S.a + i) = gload_u4(src + i);
-        for (int i = n16 + t; i < n; i += kLcThreads)
-            S.a[i] = src[i];
+    if (raw)
         len = n;
-        __syncthreads();
-    }
+    // offsets: stored bytes by wave 0, outliers by wave 1
     if (t < 64) {
         const uint64_t b = lookback(J.lb_c, c, (uint64_t)len);
         if (t == 0)
             S.base = b;
+    } else if (t < 128 && outl) {
+        const uint64_t b = lookback(J.lb_d, c, (uint64_t)zt);
+        if (t == 64)
+            S.zbase = b;
     }
     __syncthreads();
     uint64_t o_sizes, o_data;
@@ -465,9 +798,33 @@ __global__ __launch_bounds__(kLcThreads) void k_lc_encode(const Job *__restrict_
     const uint64_t cap = J.cap;
     HIZ_GLOBAL uint8_t *out = gmem(J.stream);
     const uint64_t dst = o_data + S.base;
-    for (int i = t; i < len; i += kLcThreads)
-        if (dst + i < cap)
-            out[dst + i] = S.a[i];
+    const int room = dst >= cap ? 0 : (int)min<uint64_t>((uint64_t)len, cap - dst);
+    if (raw)
+        copy_out(out + dst, FromGlobal{src}, room);
+    else
+        copy_out(out + dst, FromLds{S.a}, room);
+    if (outl) {
+        const int ib = J.idx_bytes;
+        const uint64_t oidx = st->off_oidx, oval = st->off_oval;
+#pragma unroll
+        for (int r = 0; r < kBitRounds; r++) {
+            uint64_t z = S.zbase + zbefore[r];
+            for (uint32_t m = zero[r]; m; m &= m - 1) {
+                const uint64_t gi = lo + 32 * (kLcThreads * r + t) + (__ffs((int)m) - 1);
+                if (oidx + (z + 1) * ib <= cap) {
+                    if (ib == 4)
+                        reinterpret_cast<HIZ_GLOBAL uint32_t *>(out + oidx)[z] = (uint32_t)gi;
+                    else
+                        reinterpret_cast<HIZ_GLOBAL uint64_t *>(out + oidx)[z] = gi;
+                }
+                if (oval + (z + 1) * 4 <= cap)
+                    reinterpret_cast<HIZ_GLOBAL float *>(out + oval)[z] = gmem(J.field)[gi];
+                z++;
+            }
+        }
+        if (c == n_lc - 1 && t == 0 && S.zbase + zt != st->n_out)
+            atomicOr(&st->flags, (uint32_t)ST_CORRUPT);
+    }
     if (t == 0) {
         if (o_sizes + 4 * (c + 1) <= cap)
             reinterpret_cast<HIZ_GLOBAL uint32_t *>(out + o_sizes)[c] = (uint32_t)len;
@@ -496,15 +853,16 @@ __global__ __launch_bounds__(kLcThreads) void k_lc_encode(const Job *__restrict_
 }
 
 // ---- decompression: one workgroup per chunk ---------------------------------
-__global__ __launch_bounds__(kLcThreads) void k_lc_decode(const Job *__restrict__ jobs, int njobs,
-                                                          uint64_t total, Counters *cnt)
+__global__ __launch_bounds__(kLcThreads, 4) void k_lc_decode(const Job *__restrict__ jobs,
+                                                             int njobs, uint64_t total,
+                                                             Counters *cnt)
 {
     __shared__ LcShared S;
     const int t = threadIdx.x;
     if (t == 0)
         S.id = atomicAdd(&cnt->lc_next, 1u);
     __syncthreads();
-    const uint64_t id = S.id;
+    const uint64_t id = uni32(S.id);
     if (id >= total)
         return;
     const Job &J = jobs[find_job<WK_LC>(jobs, njobs, id)];
@@ -521,22 +879,75 @@ __global__ __launch_bounds__(kLcThreads) void k_lc_decode(const Job *__restrict_
         if (t == 0)
             S.base = b;
     }
-    if (t == 0)
-        S.flag = 0;
     __syncthreads();
-    bool bad = size > (uint32_t)n || S.base + size > J.lc_bytes ||
-               (c == J.n_lc - 1 && S.base + size != J.lc_bytes);
-    int len = -1;
-    if (!bad) {
-        HIZ_GLOBAL const uint8_t *src = in + J.off_lcdata + S.base;
-        for (int i = t; i < (int)size; i += kLcThreads)
-            S.a[i] = src[i];
-        __syncthreads();
-        len = size == (uint32_t)n ? n
-              : tp ? pipe_backward<PIPE_TP>(S, (int)size) : pipe_backward<PIPE_CR>(S, (int)size);
-        bad = len != n;
-    }
+    const uint64_t base = uni64(S.base);
+    bool bad = size > (uint32_t)n || base + size > J.lc_bytes ||
+               (c == J.n_lc - 1 && base + size != J.lc_bytes);
     HIZ_GLOBAL uint8_t *dst = tp ? gmem(J.seq) + lo : gmem(J.hpay) + lo;
+    int zeros = 0; // code-0 count, checked against the outlier count
+    if (!bad) {
+        HIZ_GLOBAL const uint8_t *src = in + J.off_lcdata + base;
+        if (size == (uint32_t)n) { // stored as it is
+            copy_out(dst, FromGlobal{src}, n);
+            if (tp) {
+                for (int i = kPiece * t; i < n; i += kRound) {
+                    if (i + kPiece <= n) {
+                        const u4_any v = *reinterpret_cast<HIZ_GLOBAL const u4_any *>(src + i);
+                        zeros += 16 - __popc(nonzero4(v.x)) - __popc(nonzero4(v.y)) -
+                                 __popc(nonzero4(v.z)) - __popc(nonzero4(v.w));
+                    } else {
+                        for (int k = i; k < n; k++)
+                            zeros += src[k] == 0;
+                    }
+                }
+            }
+        } else {
+            for (int i = kPiece * t; i < (int)size; i += kRound) {
+                if (i + kPiece <= (int)size)
+                    *reinterpret_cast<u4_lds *>(S.a + i) =
+                        *reinterpret_cast<HIZ_GLOBAL const u4_any *>(src + i);
+                else
+                    for (int k = i; k < (int)size; k++)
+                        S.a[k] = src[k];
+            }
+            __syncthreads();
+            if (tp) {
+                bad = st_restore<1, false, kRounds>(
+                          S.a, (int)size, n,
+                          [&](int r, const uint4 &x) __attribute__((always_inline)) {
+                              *reinterpret_cast<uint4 *>(S.b + kRound * r + kPiece * t) = x;
+                          },
+                          S) < 0;
+                if (!bad)
+                    zeros = st_planes_inv(S.b, n, dst);
+            } else {
+                // the length of what RRE_4 gave is in front of it
+                const int n1 = st_restore<1, true, kMidRounds>(
+                    S.a, (int)size, -1,
+                    [&](int r, uint4 x) __attribute__((always_inline)) {
+                        const int i = kRound * r + kPiece * t;
+                        tcms8_piece<true>(x, i, S.a[0] | S.a[1] << 8);
+                        *reinterpret_cast<uint4 *>(S.b + i) = x;
+                    },
+                    S);
+                bad = n1 < 0 || st_restore<4, false, kRounds>(
+                                    S.b, n1, n,
+                                    [&](int r, const uint4 &x) __attribute__((always_inline)) {
+                                        const int i = kRound * r + kPiece * t;
+                                        if (i + kPiece <= n) {
+                                            gstore_u4(dst + i, x);
+                                        } else {
+                                            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                                            for (int k = 0; k < kPiece; k++)
+                                                if (i + k < n)
+                                                    dst[i + k] = (uint8_t)(w[k / 4] >> (8 * (k & 3)));
+                                        }
+                                    },
+                                    S) < 0;
+            }
+        }
+    }
     if (bad) {
         if (t == 0)
             atomicOr(&st->flags, (uint32_t)ST_CORRUPT);
@@ -544,20 +955,11 @@ __global__ __launch_bounds__(kLcThreads) void k_lc_decode(const Job *__restrict_
             dst[i] = 0;
         return;
     }
-    const int n16 = n & ~15;
-    for (int i = 16 * t; i < n16; i += 16 * kLcThreads)
-        gstore_u4(dst + i, *reinterpret_cast<const uint4 *>(S.a + i));
-    for (int i = n16 + t; i < n; i += kLcThreads)
-        dst[i] = S.a[i];
     if (tp) {
-        // code-0 count, checked against the outlier count
-        int z = 0;
-        for (int i = t; i < n; i += kLcThreads)
-            z += S.a[i] == 0;
         for (int o = 32; o > 0; o >>= 1)
-            z += __shfl_xor(z, o, 64);
-        if ((t & 63) == 0 && z)
-            atomicAdd((unsigned long long *)&st->zeros_seen, (unsigned long long)z);
+            zeros += __shfl_xor(zeros, o, 64);
+        if ((t & 63) == 0 && zeros)
+            atomicAdd((unsigned long long *)&st->zeros_seen, (unsigned long long)zeros);
     }
 }
 
