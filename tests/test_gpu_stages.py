@@ -1,13 +1,15 @@
-"""GPU: the bitwise-redundancy stages at the edges of their pieces, against the CPU oracle, byte for
+"""GPU: the bitwise-redundancy stages and the reordering at the edges of their pieces, against the CPU oracle, byte for
 byte.
 
 A thread of the stages works on 16 or 32 bytes of a 16384-byte chunk, four groups of eight bytes at a time where the
 planes allow it; a bitmap has one to four levels. The lengths end short of, on and past those edges in the last chunk.
-The fields leave few marks, many, all of them (chunks stored as they are) and outliers.
+The fields leave few marks, many, all of them (chunks stored as they are) and outliers. The reordering takes 16 points
+of a row at a time, of rows on every level.
 """
 import numpy as np
 import pytest
 
+import fieldgen as G
 import oracle as O
 from test_gpu_pipelines import check, ctx, hz  # noqa: F401  (hz, ctx: the shared fixtures)
 
@@ -38,3 +40,10 @@ def line(kind, n):
 def test_lengths(hz, ctx, kind, pipeline):
     for n in LENGTHS:
         check(hz, ctx, line(kind, n), pipeline, False, eb=1e-5 if kind == "spikes" else 1e-3, chunk=256)
+
+
+@pytest.mark.parametrize("dz", [1, 7, 15, 16, 17, 31, 32, 33, 47, 50])
+@pytest.mark.parametrize("dxy", [(1, 1), (2, 3), (5, 6), (17, 18), (34, 9)])
+def test_reordered_rows(hz, ctx, dxy, dz):
+    x = G.grf(dxy + (dz,), 3.0, 100 * dxy[0] + dz)
+    check(hz, ctx, x, O.PIPE_TP, True, eb=1e-4)
