@@ -203,6 +203,20 @@ hiz_status hiz_decompress_batch(hiz_ctx *ctx, int n, const void *const *d_ins,
                                 const uint64_t *in_sizes, float *const *d_fields,
                                 const uint64_t *field_caps, uint64_t *dims_out,
                                 hiz_status *statuses, hiz_stream_t stream);
+/* Decompression in two steps that wait for the device once for all headers. A
+ * caller needs a stream's dims before it can allocate its field: the first call
+ * reads the first HIZ_HEADER_BYTES bytes (or all, if fewer) of n streams to
+ * host memory, HIZ_HEADER_BYTES apart (for hiz_inspect), and synchronizes
+ * `stream`; the second one is hiz_decompress_batch with them, and does not read
+ * them from the device again. */
+#define HIZ_HEADER_BYTES 384
+hiz_status hiz_read_headers(hiz_ctx *ctx, int n, const void *const *d_ins,
+                            const uint64_t *in_sizes, void *h_hdrs, hiz_stream_t stream);
+hiz_status hiz_decompress_batch_headers(hiz_ctx *ctx, int n, const void *const *d_ins,
+                                        const uint64_t *in_sizes, const void *h_hdrs,
+                                        float *const *d_fields, const uint64_t *field_caps,
+                                        uint64_t *dims_out, hiz_status *statuses,
+                                        hiz_stream_t stream);
 hiz_status hiz_compress_batch_submit(hiz_ctx *ctx, int n, const float *const *d_fields,
                                      const uint64_t *dims, const int *modes, const double *ebs,
                                      const hiz_params *params, void *const *d_outs,

@@ -194,6 +194,9 @@ int encode_blocks_per_cu();
 
 void launch_fill(float *out, uint64_t n, float v, hipStream_t s);
 void launch_gather_results(const Job *d_jobs, int njobs, void *h_dst, hipStream_t s);
+// The first bytes of n streams, kOffChunks apart in h_dst; h_tab: n {address, size}.
+// Both in pinned host memory.
+void launch_gather_headers(const uint64_t *h_tab, int n, void *h_dst, hipStream_t s);
 void launch_init_decompress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_blocks,
                             Counters *cnt, hipStream_t s);
 void launch_dec_tables(const Job *d_jobs, int njobs, uint64_t max_blocks, hipStream_t s);

@@ -612,4 +612,27 @@ void launch_gather_results(const Job *d_jobs, int njobs, void *h_dst, hipStream_
                        njobs, static_cast<uint32_t *>(h_dst));
 }
 
+// The first kOffChunks bytes (or all, if fewer) of n streams, kOffChunks apart, to
+// pinned memory; tab: n {address, size}, in pinned memory too.
+__global__ __launch_bounds__(128) void k_gather_headers(const uint64_t *__restrict__ tab,
+                                                        uint8_t *__restrict__ dst)
+{
+    const uint64_t n = min(tab[2 * blockIdx.x + 1], (uint64_t)kOffChunks);
+    HIZ_GLOBAL const uint8_t *src = gmem(reinterpret_cast<const uint8_t *>(tab[2 * blockIdx.x]));
+    dst += (uint64_t)kOffChunks * blockIdx.x;
+    if (n == kOffChunks && (reinterpret_cast<uintptr_t>(src) & 3) == 0) {
+        if (threadIdx.x < kOffChunks / 4)
+            reinterpret_cast<uint32_t *>(dst)[threadIdx.x] =
+                reinterpret_cast<HIZ_GLOBAL const uint32_t *>(src)[threadIdx.x];
+    } else {
+        for (uint64_t i = threadIdx.x; i < n; i += 128)
+            dst[i] = src[i];
+    }
+}
+
+void launch_gather_headers(const uint64_t *h_tab, int n, void *h_dst, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_gather_headers, dim3(n), dim3(128), 0, s, h_tab, static_cast<uint8_t *>(h_dst));
+}
+
 } // namespace hiz

@@ -1276,6 +1276,38 @@ hiz_status submit_decompress(hiz_ctx *c, int n, const void *const *d_ins,
     return rc ? abandon(c, s, rc) : rc;
 }
 
+// The streams' first bytes, by one launch into pinned memory and one wait.
+hiz_status read_headers(hiz_ctx *c, int n, const void *const *d_ins, const uint64_t *in_sizes,
+                        uint8_t *h_hdrs, hipStream_t s)
+{
+    c->err.clear();
+    if (n < 0 || n > kMaxBatch)
+        return fail(c, HIZ_ERR_ARG, "batch size must be in [0, %d]", kMaxBatch);
+    if (n > 0 && (!d_ins || !in_sizes || !h_hdrs))
+        return fail(c, HIZ_ERR_ARG, "NULL argument");
+    if (c->batch.pending)
+        return fail(c, HIZ_ERR_ARG, "the previous batch on this context is not finished");
+    if (n == 0)
+        return HIZ_OK;
+    HIP_TRY(c, hipSetDevice(c->device));
+    const uint64_t o_hdr = align16(16ull * n);
+    hiz_status rc = ensure_pinned(c, o_hdr + (uint64_t)kOffChunks * n);
+    if (rc)
+        return rc;
+    uint64_t *tab = reinterpret_cast<uint64_t *>(c->pinned);
+    for (int i = 0; i < n; i++) {
+        tab[2 * i] = reinterpret_cast<uintptr_t>(d_ins[i]);
+        tab[2 * i + 1] = d_ins[i] ? std::min<uint64_t>(in_sizes[i], kOffChunks) : 0;
+    }
+    launch_gather_headers(tab, n, c->pinned + o_hdr, s);
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipStreamSynchronize(s));
+    for (int i = 0; i < n; i++)
+        memcpy(h_hdrs + (uint64_t)kOffChunks * i, c->pinned + o_hdr + (uint64_t)kOffChunks * i,
+               tab[2 * i + 1]);
+    return HIZ_OK;
+}
+
 // Wait for the pending batch and turn its device results into per-field
 // statuses and sizes. Returns the first failing field's status.
 hiz_status finish(hiz_ctx *c, uint64_t *sizes, uint64_t *dims, hiz_status *statuses)
@@ -1564,6 +1596,7 @@ uint64_t hiz_workspace_bound(const uint64_t dims[3])
 } // extern "C"
 
 namespace hiz {
+static_assert(kOffChunks == HIZ_HEADER_BYTES, "published header length");
 // Pinned staging of a context for batches of up to n fields, allocated now so
 // that no later call of that size reallocates it.
 hiz_status ctx_reserve_pinned(hiz_ctx *c, int n)
@@ -1743,6 +1776,29 @@ hiz_status hiz_decompress_batch(hiz_ctx *c, int n, const void *const *d_ins,
         return HIZ_ERR_ARG;
     hiz_status rc = submit_decompress(c, n, d_ins, in_sizes, d_fields, field_caps,
                                       reinterpret_cast<hipStream_t>(stream));
+    return rc ? rc : finish(c, nullptr, dims_out, statuses);
+}
+
+hiz_status hiz_read_headers(hiz_ctx *c, int n, const void *const *d_ins, const uint64_t *in_sizes,
+                            void *h_hdrs, hiz_stream_t stream)
+{
+    if (!c)
+        return HIZ_ERR_ARG;
+    return read_headers(c, n, d_ins, in_sizes, static_cast<uint8_t *>(h_hdrs),
+                        reinterpret_cast<hipStream_t>(stream));
+}
+
+hiz_status hiz_decompress_batch_headers(hiz_ctx *c, int n, const void *const *d_ins,
+                                        const uint64_t *in_sizes, const void *h_hdrs,
+                                        float *const *d_fields, const uint64_t *field_caps,
+                                        uint64_t *dims_out, hiz_status *statuses,
+                                        hiz_stream_t stream)
+{
+    if (!c || (n > 0 && !h_hdrs))
+        return HIZ_ERR_ARG;
+    hiz_status rc = submit_decompress(c, n, d_ins, in_sizes, d_fields, field_caps,
+                                      reinterpret_cast<hipStream_t>(stream),
+                                      static_cast<const uint8_t *>(h_hdrs));
     return rc ? rc : finish(c, nullptr, dims_out, statuses);
 }
 

@@ -28,7 +28,9 @@ SYMBOLS = ["hiz_create", "hiz_destroy", "hiz_last_error", "hiz_compress_bound",
            "hiz_decompress_batch_submit", "hiz_batch_ready", "hiz_batch_finish", "hiz_set_graphs",
            "hiz_graph_stats", "hiz_server_create", "hiz_server_submit", "hiz_server_poll",
            "hiz_server_drain", "hiz_server_get_stats", "hiz_server_clock", "hiz_server_destroy",
-           "hiz_set_profiling", "hiz_get_profile", "hiz_reset_profile", "hiz_compress_noalloc"]
+           "hiz_set_profiling", "hiz_get_profile", "hiz_reset_profile", "hiz_compress_noalloc",
+           "hiz_read_headers", "hiz_decompress_batch_headers"]
+HEADER_BYTES = 384
 OP_COMPRESS, OP_DECOMPRESS = 0, 1
 
 
@@ -110,6 +112,9 @@ def lib():
                                              C.POINTER(Params), vpp, u64p, u64p, ip, C.c_void_p]
             L.hiz_decompress_batch.argtypes = [C.c_void_p, C.c_int, vpp, u64p, vpp, u64p, u64p,
                                                ip, C.c_void_p]
+            L.hiz_read_headers.argtypes = [C.c_void_p, C.c_int, vpp, u64p, C.c_void_p, C.c_void_p]
+            L.hiz_decompress_batch_headers.argtypes = [C.c_void_p, C.c_int, vpp, u64p, C.c_void_p,
+                                                       vpp, u64p, u64p, ip, C.c_void_p]
             L.hiz_compress_batch_submit.argtypes = [C.c_void_p, C.c_int, vpp, u64p, ip, dp,
                                                     C.POINTER(Params), vpp, u64p, C.c_void_p]
             L.hiz_decompress_batch_submit.argtypes = [C.c_void_p, C.c_int, vpp, u64p, vpp, u64p,
@@ -290,6 +295,41 @@ class Context:
                                      out.numel(), params, sh)
         return out[:size]
 
+    def _decompress_headers(self, streams, hdrs, outs, what="decompress"):
+        """Decode streams whose headers are on the host; the fields' statuses (one field alone
+        raises)."""
+        n = len(streams)
+        st = (C.c_int * n)()
+        rc = lib().hiz_decompress_batch_headers(
+            self._h, n, (C.c_void_p * n)(*[s_.data_ptr() for s_ in streams]),
+            (C.c_uint64 * n)(*[s_.numel() for s_ in streams]), hdrs,
+            (C.c_void_p * n)(*[o.data_ptr() for o in outs]),
+            (C.c_uint64 * n)(*[o.numel() for o in outs]), None, st, _stream_handle(None))
+        if rc and (what == "decompress" or not any(st)):
+            raise self._err(rc, what)
+        return list(st)
+
+    def _read_headers(self, streams, stream):
+        """The streams' headers on the host (HEADER_BYTES apart), read on the stream the decoding
+        will run on; None where that is not the streams' device's current one, or if it fails:
+        then each header is read through its tensor."""
+        import torch
+        n = len(streams)
+        if n == 0 or stream is not None or torch.cuda.current_device() != self.device \
+                or any(s_.device.index != self.device for s_ in streams):
+            return None
+        hdrs = C.create_string_buffer(HEADER_BYTES * n)
+        rc = lib().hiz_read_headers(self._h, n, (C.c_void_p * n)(*[s_.data_ptr() for s_ in streams]),
+                                    (C.c_uint64 * n)(*[s_.numel() for s_ in streams]), hdrs,
+                                    _stream_handle(None))
+        return None if rc else hdrs
+
+    @staticmethod
+    def _header(hdrs, i, stream_t):
+        if hdrs is None:
+            return stream_t[:512].cpu().numpy().tobytes()
+        return hdrs[HEADER_BYTES * i:HEADER_BYTES * i + min(stream_t.numel(), HEADER_BYTES)]
+
     def decompress(self, stream_t, out=None, stream=None, squeeze=False):
         """Decompress a uint8 CUDA tensor holding one stream; returns float32 (dx, dy, dz),
         or with squeeze=True without the leading size-1 axes of a 2-D or 1-D field."""
@@ -297,13 +337,16 @@ class Context:
         if stream_t.dtype != torch.uint8 or not stream_t.is_cuda:
             raise ValueError("decompress needs a uint8 tensor on a HIP device")
         stream_t = stream_t.contiguous()
-        info = inspect(stream_t[:512].cpu().numpy().tobytes())
-        shape = info["dims"]
+        hdrs = self._read_headers([stream_t], stream)
+        shape = inspect(self._header(hdrs, 0, stream_t))["dims"]
         n = shape[0] * shape[1] * shape[2]
         if out is None:
             out = torch.empty(shape, dtype=torch.float32, device=stream_t.device)
-        self.decompress_ptr(stream_t.data_ptr(), stream_t.numel(), out.data_ptr(), out.numel(),
-                            _stream_handle(stream))
+        if hdrs is None:
+            self.decompress_ptr(stream_t.data_ptr(), stream_t.numel(), out.data_ptr(), out.numel(),
+                                _stream_handle(stream))
+        else:
+            self._decompress_headers([stream_t], hdrs, [out])
         y = out.view(shape) if out.numel() == n else out
         if squeeze and out.numel() == n:
             while y.dim() > 1 and y.shape[0] == 1:
@@ -420,13 +463,17 @@ class Context:
         """Decompress a list of uint8 CUDA tensors in one batch; returns float32 tensors."""
         import torch
         streams = [s_.contiguous() for s_ in streams]
-        shapes = [inspect(s_[:512].cpu().numpy().tobytes())["dims"] for s_ in streams]
+        hdrs = self._read_headers(streams, stream)
+        shapes = [inspect(self._header(hdrs, i, s_))["dims"] for i, s_ in enumerate(streams)]
         outs = [torch.empty(sh_, dtype=torch.float32, device=s_.device)
                 for sh_, s_ in zip(shapes, streams)]
-        dims, st = self.decompress_batch_ptr([s_.data_ptr() for s_ in streams],
-                                             [s_.numel() for s_ in streams],
-                                             [o.data_ptr() for o in outs],
-                                             [o.numel() for o in outs], _stream_handle(stream))
+        if hdrs is None:
+            dims, st = self.decompress_batch_ptr([s_.data_ptr() for s_ in streams],
+                                                 [s_.numel() for s_ in streams],
+                                                 [o.data_ptr() for o in outs],
+                                                 [o.numel() for o in outs], _stream_handle(stream))
+        else:
+            st = self._decompress_headers(streams, hdrs, outs, "decompress_batch")
         for i, s_ in enumerate(st):
             if s_:
                 raise HizError(s_, f"decompress_batch field {i}: "
