@@ -3,6 +3,7 @@
 // kernels write, and the host-side launchers of every kernel.
 #pragma once
 
+#include <type_traits>
 #include "hiz.h"
 
 #include <hip/hip_runtime.h>
@@ -361,18 +362,28 @@ __device__ inline void copy_job(Job &J, const Job *h_jobs, Job *d_jobs)
 // of wave 0 (other threads get partial values). `red` is 8 words of LDS.
 __device__ inline void block_minmax(uint32_t &kmn, uint32_t &kmx, uint32_t *red)
 {
-    for (int o = 32; o > 0; o >>= 1) {
-        kmn = min(kmn, (uint32_t)__shfl_xor((int)kmn, o, 64));
-        kmx = max(kmx, (uint32_t)__shfl_xor((int)kmx, o, 64));
-    }
+    // DPP: towards the last lane of each row of 16, then of the wave (a lane
+    // without a source keeps its value)
+    auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+        constexpr int c = decltype(ctrl)::value, r = decltype(rows)::value;
+        kmn = min(kmn, (uint32_t)__builtin_amdgcn_update_dpp((int)kmn, (int)kmn, c, r, 0xf, false));
+        kmx = max(kmx, (uint32_t)__builtin_amdgcn_update_dpp((int)kmx, (int)kmx, c, r, 0xf, false));
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>(), integral_constant<int, 0xf>()); // row_shr 1, 2, 4, 8
+    step(integral_constant<int, 0x112>(), integral_constant<int, 0xf>());
+    step(integral_constant<int, 0x114>(), integral_constant<int, 0xf>());
+    step(integral_constant<int, 0x118>(), integral_constant<int, 0xf>());
+    step(integral_constant<int, 0x142>(), integral_constant<int, 0xa>()); // row_bcast 15, 31
+    step(integral_constant<int, 0x143>(), integral_constant<int, 0xc>());
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
+    if (lane == 63) {
         red[2 * wv] = kmn;
         red[2 * wv + 1] = kmx;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); w++) {
+        for (int w = 0; w < (int)(blockDim.x >> 6); w++) {
             kmn = min(kmn, red[2 * w]);
             kmx = max(kmx, red[2 * w + 1]);
         }

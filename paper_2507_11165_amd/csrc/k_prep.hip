@@ -263,9 +263,12 @@ void launch_eps(const Job *d_jobs, int njobs, uint32_t mm_grid, hipStream_t s)
 // target costs three splines' errors along each of its odd axes and, with more
 // than one, of their combination; they are added up apart for each class of
 // targets (which axes are odd) and handed out to the candidates once per class.
-// What bounds it is the latency of one workgroup: with all 21 errors formed per
-// target 26 us at 64^3, 39 at 512^3 and 28 for a 1800 x 3600 field; this way 21,
-// 28 and 18.
+// A wave takes 64 targets of one class at a time; had each class been spread over
+// the workgroup, its part of it (85 targets of stride 1) would leave two thirds of
+// the lanes idle. What bounds the kernel is the latency of one workgroup: loads,
+// three of those units, the sums. With all 21 errors formed per target, and the
+// bound and the choice left to launches of their own, the three took 39 us at 64^3,
+// 53 at 512^3 and 41 for a 1800 x 3600 field; this way one takes 20, 26 and 20.
 // ---------------------------------------------------------------------------
 constexpr int kTuneParts = 9;
 
@@ -356,7 +359,8 @@ __device__ __forceinline__ uint64_t wave_sum_dpp64(uint64_t v)
 // n (g0 + 1) / parts.
 template <int M>
 __device__ __forceinline__ void tune_class(const float *__restrict__ blk, const int E[3], int s,
-                                           int part, int parts, double scale, uint64_t acc[kCands])
+                                           int &unit, int &base, int waves, double scale,
+                                           uint64_t acc[kCands])
 {
     const int K = 8 / s; // odd multiples of s in a block; even ones: one more
     int n[3];
@@ -366,8 +370,15 @@ __device__ __forceinline__ void tune_class(const float *__restrict__ blk, const 
     constexpr bool MULTI = (M & (M - 1)) != 0;
     uint64_t one[3][3] = {}, md[3] = {}; // [spline][axis]; multi-dimensional
     int terms = 0;
-    for (int g = part * total / parts + (int)threadIdx.x; g < (part + 1) * total / parts;
-         g += blockDim.x) {
+    const int end = base + (total + 63) / 64;
+    if (unit >= end) {
+        base = end;
+        return;
+    }
+    for (; unit < end; unit += waves) {
+        const int g = 64 * (unit - base) + (int)(threadIdx.x & 63);
+        if (g >= total)
+            continue;
         const int iz = g % n[2], r = g / n[2], iy = r % n[1], ix = r / n[1];
         const int t[3] = {(2 * ix + (M & 1)) * s, (2 * iy + ((M >> 1) & 1)) * s,
                           (2 * iz + (M >> 2)) * s};
@@ -397,6 +408,7 @@ __device__ __forceinline__ void tune_class(const float *__restrict__ blk, const 
                 md[sp] += tune_term(x, md_combine(p[sp], rk[sp], M), scale);
         terms++;
     }
+    base = end;
     const uint64_t bias = (uint64_t)terms * kTermBias;
     constexpr int first = (M & 1) ? 0 : ((M & 2) ? 1 : 2);
 #pragma unroll
@@ -412,16 +424,19 @@ __device__ __forceinline__ void tune_class(const float *__restrict__ blk, const 
         }
     }
 }
-__device__ void tune_level(const float *__restrict__ blk, const int E[3], int s, int part, int parts,
+// The targets of a level, in units of a class's 64 (base: the first of a class),
+// dealt out to `waves` waves of which this is the one numbered `unit`.
+__device__ void tune_level(const float *__restrict__ blk, const int E[3], int s, int unit, int waves,
                            double scale, uint64_t acc[kCands])
 {
-    tune_class<1>(blk, E, s, part, parts, scale, acc);
-    tune_class<2>(blk, E, s, part, parts, scale, acc);
-    tune_class<3>(blk, E, s, part, parts, scale, acc);
-    tune_class<4>(blk, E, s, part, parts, scale, acc);
-    tune_class<5>(blk, E, s, part, parts, scale, acc);
-    tune_class<6>(blk, E, s, part, parts, scale, acc);
-    tune_class<7>(blk, E, s, part, parts, scale, acc);
+    int base = 0;
+    tune_class<7>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<6>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<5>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<3>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<4>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<2>(blk, E, s, unit, base, waves, scale, acc);
+    tune_class<1>(blk, E, s, unit, base, waves, scale, acc);
 }
 
 __device__ void tune_flush(FieldState *st, int level, uint64_t acc[kCands], uint64_t *red)
@@ -488,12 +503,16 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
     if (st->flags & ST_NONFINITE)
         return;
     const uint64_t lu = u - J.tune_begin;
-    const uint64_t j = lu / kTuneParts;
-    const int part = (int)(lu % kTuneParts);
+    const uint64_t j = (uint32_t)lu / (uint32_t)kTuneParts; // (a launch has fewer than 2^32 units)
+    const int part = (int)((uint32_t)lu - (uint32_t)j * kTuneParts);
+    // (divisions in 32 bits where they do)
+    auto div = [](uint64_t a, uint64_t b) __attribute__((always_inline)) -> uint64_t {
+        return (a | b) >> 32 ? a / b : (uint64_t)((uint32_t)a / (uint32_t)b);
+    };
     const uint64_t n_full = (uint64_t)J.n_full[0] * J.n_full[1] * J.n_full[2];
-    const uint64_t idx = ((2 * j + 1) * n_full) / (2 * (uint64_t)J.n_samples);
-    const uint64_t bc = idx % J.n_full[2], bb = (idx / J.n_full[2]) % J.n_full[1],
-                   ba = idx / ((uint64_t)J.n_full[1] * J.n_full[2]);
+    const uint64_t idx = div((2 * j + 1) * n_full, 2 * (uint64_t)J.n_samples);
+    const uint64_t row = div(idx, J.n_full[2]), ba = div(row, J.n_full[1]);
+    const uint64_t bc = idx - row * J.n_full[2], bb = row - ba * J.n_full[1];
     const uint64_t dy = J.dims[1], dz = J.dims[2];
     // a full block spans 17 points per axis, 1 on a flat axis (2-D / 1-D fields)
     const int E[3] = {J.dims[0] == 1 ? 1 : kSide, J.dims[1] == 1 ? 1 : kSide,
@@ -545,10 +564,10 @@ __global__ __launch_bounds__(256) void k_tune(const Job *__restrict__ jobs, int 
     const int l0 = part == 0 ? 0 : (part <= 2 ? 2 : 3), l1 = part == 0 ? 1 : l0;
 #pragma unroll 1
     for (int l = l0; l <= l1; l++) {
-        if (part == 0)
-            tune_level(blk, E, 8 >> l, 0, 1, scale, acc);
-        else
-            tune_level(blk, E, 8 >> l, part <= 2 ? part - 1 : part - 3, part <= 2 ? 2 : 6, scale, acc);
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int p = part == 0 ? 0 : part <= 2 ? part - 1 : part - 3;
+        const int parts = part == 0 ? 1 : part <= 2 ? 2 : 6;
+        tune_level(blk, E, 8 >> l, 4 * p + wave, 4 * parts, scale, acc);
         tune_flush(st, l, acc, red);
     }
     // The field's last workgroup picks: every workgroup's sums are in place
