@@ -154,6 +154,10 @@ __global__ __launch_bounds__(256) void k_codebook(const Job *__restrict__ jobs, 
     __shared__ int s_maxlen;
     uint32_t *w32 = reinterpret_cast<uint32_t *>(w);
     const int t = threadIdx.x;
+    // throughput mode: no Huffman stage, every code length 0
+    const uint64_t count = J.pipe == PIPE_TP ? 0 : st->hist[t];
+    for (int k = t; k < 4 * (kMaxCodeLen + 1); k += 256)
+        (&wcnt[0][0])[k] = 0;
     const uint32_t flags = st->flags;
     if (flags & ST_NONFINITE)
         return;
@@ -197,8 +201,7 @@ __global__ __launch_bounds__(256) void k_codebook(const Job *__restrict__ jobs, 
         return;
     }
 
-    // throughput mode: no Huffman stage, every code length 0
-    cnt[t] = J.pipe == PIPE_TP ? 0 : st->hist[t];
+    cnt[t] = count;
     for (;;) {
         __syncthreads();
         const uint64_t c = cnt[t];
@@ -264,23 +267,27 @@ __global__ __launch_bounds__(256) void k_codebook(const Job *__restrict__ jobs, 
     const int L = len[t];
     const int wv = t >> 6, lane = t & 63;
     const int maxlen = s_maxlen;
-    uint32_t rank = 0;
-    for (int b = 1; b <= maxlen; b++) {
-        const uint64_t same = __ballot(L == b);
-        if (L == b)
-            rank = (uint32_t)__popcll(same & ((1ull << lane) - 1));
-        if (lane == 0)
-            wcnt[wv][b] = (uint32_t)__popcll(same);
+    // lanes of this one's length, bit by bit of it
+    static_assert(kMaxCodeLen < 64, "six bits");
+    uint64_t same = ~0ull;
+#pragma unroll
+    for (int b = 0; b < 6; b++) {
+        const uint64_t on = __ballot(L >> b & 1);
+        same &= L >> b & 1 ? on : ~on;
     }
+    uint32_t rank = (uint32_t)__popcll(same & ((1ull << lane) - 1));
+    if (rank == 0)
+        wcnt[wv][L] = (uint32_t)__popcll(same);
     __syncthreads();
-    if (t == 0) {
-        uint64_t code = 0;
-        uint32_t before = 0; // symbols of the length before
-        for (int b = 1; b <= maxlen; b++) {
-            code = (code + before) << 1;
-            nextc[b] = code;
-            before = wcnt[0][b] + wcnt[1][b] + wcnt[2][b] + wcnt[3][b];
-        }
+    if (t < 64) {
+        // lane b: the codes of length b, in units of the longest length's; what
+        // comes before them all is the first of them
+        uint64_t x = 0;
+        if (t >= 1 && t <= maxlen)
+            x = (uint64_t)(wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t]) << (maxlen - t);
+        const uint64_t before = wave_incl_scan64(x) - x;
+        if (t >= 1 && t <= maxlen)
+            nextc[t] = before >> (maxlen - t);
     }
     __syncthreads();
     uint32_t mycode = 0;
