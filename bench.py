@@ -63,7 +63,7 @@ def algorithmic_bytes(name, N, info, n_anchors):
     read once (and once more for the exact range in REL mode), the anchors,
     the outliers (index + value), the Huffman payload and its chunk table,
     and the reconstructed field written once. Intermediates of this
-    implementation (the code array, the coarse pre-pass slots, tables) count
+    implementation (the code array, tables) count
     zero. None for kernels that move no algorithmic bytes."""
     n_out = info["n_outliers"]
     pw = info["payload_words"]
@@ -351,10 +351,8 @@ def main():
     step_bytes = step_algorithmic_bytes(N, info, n_anchors)
     step_s = elapsed / args.steps
     # measured HBM bytes of one step: every kernel's counted traffic (all of
-    # them must have current counters; the coarse pre-pass kernels are listed
-    # under their own names)
-    traffic_names = ["minmax", "coarse", "predict_quant", "encode", "decode",
-                     "coarse_rec", "reconstruct"]
+    # them must have current counters)
+    traffic_names = ["minmax", "predict_quant", "encode", "decode", "reconstruct"]
     tr = [measured_traffic(k) if current else None for k in traffic_names]
     step_traffic = sum(tr) if all(tr) else None
     value = 8.0 * N * args.steps / elapsed / 1e9
@@ -413,7 +411,7 @@ def main():
             fs = field_summary(x, me)
             # mean launch time of each interpolation kernel (total / launches)
             fs["kernels_ms"] = {k: round(v[1] / max(v[0], 1), 5) for k, v in me["prof"].items()
-                                if k in ("coarse", "predict_quant", "coarse_rec", "reconstruct")}
+                                if k in ("predict_quant", "reconstruct")}
             forced[name] = fs
         res["forced_interp"] = forced
         del xd, zbuf, ybuf, x

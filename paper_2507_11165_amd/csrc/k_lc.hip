@@ -24,7 +24,7 @@
 // the instructions of those passes and, per chunk, the latency of a claim, of the
 // look-back and of some five barriers; four workgroups per compute unit (36 KB
 // of LDS each) fill in for each other. 256^3: throughput mode 134 -> 35 us
-// encoding and 87 -> 39 decoding, ratio mode 108 -> 53 and 44 -> 24, the first
+// encoding and 87 -> 39 decoding, ratio mode 108 -> 30 and 44 -> 24, the first
 // figure for loops over single bytes with a scan per bitmap level.
 #include "hiz_internal.h"
 
@@ -719,6 +719,12 @@ __global__ __launch_bounds__(kLcThreads, 4) void k_lc_encode(const Job *__restri
 {
     __shared__ LcShared S;
     const int t = threadIdx.x;
+    // One field: as many workgroups claim as there are chunks. (A payload is
+    // sized for 32 bits a code, and most of the launch has no chunk; claims, on
+    // one word, are made one after the other: 256^3 ratio mode 53 us, 30
+    // without.)
+    if (njobs == 1 && blockIdx.x >= cdiv(lc_input_bytes(jobs[0], jobs[0].st), kLcChunk))
+        return;
     if (t == 0)
         S.id = atomicAdd(&cnt->lc_next, 1u);
     __syncthreads();

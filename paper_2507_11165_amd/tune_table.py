@@ -88,8 +88,7 @@ def main():
                 ctx.set_profiling(False)
                 prof = ctx.profile()
                 ks = " ".join(f"{k}={v[1] / max(v[0], 1) * 1e3:.1f}us" for k, v in sorted(prof.items())
-                              if k in ("encode", "decode", "predict_quant", "reconstruct", "coarse",
-                                       "coarse_rec"))
+                              if k in ("encode", "decode", "predict_quant", "reconstruct"))
                 print(f"shape {shape} N {N} chunk {chunk} tile_z {tz} ms {ms:.4f} "
                       f"GBps {gbs:.1f} ratio {ratio:.4f} {ks}", flush=True)
         best_ratio = max(r[4] for r in rows)
