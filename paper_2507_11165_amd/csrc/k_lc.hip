@@ -1157,30 +1157,40 @@ __global__ __launch_bounds__(256) void k_outliers(const Job *__restrict__ jobs, 
     const uint64_t lo = u * kLcChunk;
     const int n = (int)min<uint64_t>(kLcChunk, J.N - lo);
     HIZ_GLOBAL const uint8_t *codes = gmem(J.codes) + lo;
-    constexpr int per = kLcChunk / 256; // 64 codes per thread
+    // 64 codes per thread, in a chunk's whole pieces 16 at a time (the code array
+    // starts at a multiple of 256 bytes)
+    constexpr int per = kLcChunk / 256;
     uint32_t w[per / 4];
     const int i0 = t * per;
     int z = 0;
-    if (i0 + per <= n && ((lo + i0) & 3) == 0) {
+    if (i0 + per <= n) {
 #pragma unroll
-        for (int k = 0; k < per / 4; k++) {
-            w[k] = reinterpret_cast<HIZ_GLOBAL const uint32_t *>(codes + i0)[k];
-            const uint32_t v = w[k];
-            z += ((v & 0xffu) == 0) + ((v & 0xff00u) == 0) + ((v & 0xff0000u) == 0) +
-                 ((v & 0xff000000u) == 0);
+        for (int k = 0; k < per / 16; k++) {
+            const uint4 v = gload_u4(codes + i0 + 16 * k);
+            w[4 * k] = v.x;
+            w[4 * k + 1] = v.y;
+            w[4 * k + 2] = v.z;
+            w[4 * k + 3] = v.w;
         }
     } else {
 #pragma unroll
         for (int k = 0; k < per / 4; k++) {
-            uint32_t v = 0;
+            w[k] = 0;
             for (int b = 0; b < 4; b++) {
                 const int i = i0 + 4 * k + b;
-                v |= (uint32_t)(i < n ? codes[i] : 1u) << (8 * b);
+                w[k] |= (uint32_t)(i < n ? codes[i] : 1u) << (8 * b);
             }
-            w[k] = v;
-            z += ((v & 0xffu) == 0) + ((v & 0xff00u) == 0) + ((v & 0xff0000u) == 0) +
-                 ((v & 0xff000000u) == 0);
         }
+    }
+    // bit k of zero[h]: code 32 h + k is an outlier's
+    uint32_t zero[per / 32];
+#pragma unroll
+    for (int h = 0; h < per / 32; h++) {
+        zero[h] = 0;
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            zero[h] |= (nonzero4(w[8 * h + k]) ^ 15u) << (4 * k);
+        z += __popc(zero[h]);
     }
     int zt;
     const int zb = wg_excl_scan(z, s_scan, zt);
@@ -1195,19 +1205,21 @@ __global__ __launch_bounds__(256) void k_outliers(const Job *__restrict__ jobs, 
         const uint64_t cap = J.cap;
         const int ib = J.idx_bytes;
         HIZ_GLOBAL uint8_t *out = gmem(J.stream);
-        for (int k = 0; k < per; k++) {
-            if (((w[k >> 2] >> (8 * (k & 3))) & 0xffu) != 0)
-                continue;
-            const uint64_t gi = lo + i0 + k;
-            if (st->off_oidx + (slot + 1) * ib <= cap) {
-                if (ib == 4)
-                    reinterpret_cast<HIZ_GLOBAL uint32_t *>(out + st->off_oidx)[slot] = (uint32_t)gi;
-                else
-                    reinterpret_cast<HIZ_GLOBAL uint64_t *>(out + st->off_oidx)[slot] = gi;
+        const uint64_t oidx = st->off_oidx, oval = st->off_oval;
+#pragma unroll
+        for (int h = 0; h < per / 32; h++) {
+            for (uint32_t m = zero[h]; m; m &= m - 1) {
+                const uint64_t gi = lo + i0 + 32 * h + (__ffs((int)m) - 1);
+                if (oidx + (slot + 1) * ib <= cap) {
+                    if (ib == 4)
+                        reinterpret_cast<HIZ_GLOBAL uint32_t *>(out + oidx)[slot] = (uint32_t)gi;
+                    else
+                        reinterpret_cast<HIZ_GLOBAL uint64_t *>(out + oidx)[slot] = gi;
+                }
+                if (oval + (slot + 1) * 4 <= cap)
+                    reinterpret_cast<HIZ_GLOBAL float *>(out + oval)[slot] = gmem(J.field)[gi];
+                slot++;
             }
-            if (st->off_oval + (slot + 1) * 4 <= cap)
-                reinterpret_cast<HIZ_GLOBAL float *>(out + st->off_oval)[slot] = gmem(J.field)[gi];
-            slot++;
         }
     }
     if (t == 0 && u == J.n_ou - 1 && s_base + zt != st->n_out)
