@@ -156,16 +156,19 @@ int ilog2(uint64_t v)
 // the highest compress + decompress throughput among those whose compression
 // ratio is within 1 % of the best ratio, and the fastest tile depth for it. A
 // field takes the row nearest to it in (log N, log dz); a tile depth above the
-// field's block count along z is lowered to it.
+// field's block count along z is lowered to it. One block per tile is no row's
+// pick: 64^3 takes k_predict 39 us against 37 with two, and a batch of mixed
+// sizes needs one launch of each tile kernel where it needed two (24 fields of
+// sides 32..160: k_predict 204 -> 168 us, k_reconstruct 176 -> 143).
 struct LaunchRow {
     uint64_t dims[3];
     uint32_t chunk;
     int tz;
 };
 constexpr LaunchRow kLaunchTable[] = {
-    {{64, 64, 64}, 1024, 1},     {{128, 128, 128}, 1024, 2}, {{192, 192, 192}, 1024, 4},
-    {{256, 256, 256}, 1024, 2},  {{100, 500, 500}, 1024, 2}, {{384, 384, 384}, 1024, 2},
-    {{512, 512, 512}, 1024, 2},  {{384, 96, 48}, 1024, 1},   {{48, 96, 384}, 1024, 2},
+    {{64, 64, 64}, 1024, 2},     {{128, 128, 128}, 1024, 2}, {{192, 192, 192}, 1024, 4},
+    {{256, 256, 256}, 1024, 4},  {{100, 500, 500}, 1024, 2}, {{384, 384, 384}, 1024, 2},
+    {{512, 512, 512}, 1024, 2},  {{384, 96, 48}, 1024, 2},   {{48, 96, 384}, 1024, 2},
 };
 
 struct LaunchDefaults {
@@ -190,6 +193,12 @@ LaunchDefaults default_launch(const uint64_t dims[3])
     }
     LaunchDefaults L{best->chunk, best->tz};
     const uint64_t nbz = cdiv(dims[2], kAnchor);
+    // tiles of four blocks only where they divide the field: a last tile of one
+    // or two takes as long as a whole one (k_predict with four / two: 256^3 82 /
+    // 94 us, 192^3 54 / 62; 160^3, 10 blocks, 54 / 47, 193x301x277, 18 blocks, 102
+    // / 92)
+    if (L.tz == 4 && nbz % 4 != 0)
+        L.tz = 2;
     while (L.tz > 1 && (uint64_t)L.tz > nbz)
         L.tz >>= 1;
     return L;
