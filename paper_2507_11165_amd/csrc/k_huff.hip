@@ -784,11 +784,12 @@ __global__ __launch_bounds__(256) void k_init_decompress(const Job *__restrict__
 void launch_init_decompress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_blocks,
                             Counters *cnt, hipStream_t s)
 {
+    // (each workgroup reads its Job over the host link: 1024 of them, or one a field)
     uint64_t gx = cdiv(max_blocks, 256);
+    if (gx > 1024 / (uint64_t)njobs)
+        gx = 1024 / (uint64_t)njobs;
     if (gx < 1)
         gx = 1;
-    if (gx > 1024)
-        gx = 1024;
     hipLaunchKernelGGL(k_init_decompress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, h_jobs,
                        d_jobs, cnt);
 }

@@ -113,11 +113,12 @@ __global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ h
 void launch_init_compress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t max_chunks,
                           Counters *cnt, hipStream_t s)
 {
+    // (each workgroup reads its Job over the host link: 1024 of them, or one a field)
     uint64_t gx = cdiv(max_chunks, 256);
+    if (gx > 1024 / (uint64_t)njobs)
+        gx = 1024 / (uint64_t)njobs;
     if (gx < 1)
         gx = 1;
-    if (gx > 1024)
-        gx = 1024;
     hipLaunchKernelGGL(k_init_compress, dim3((uint32_t)gx, njobs), dim3(256), 0, s, h_jobs, d_jobs,
                        cnt);
 }
