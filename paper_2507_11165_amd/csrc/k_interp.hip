@@ -32,7 +32,7 @@
 // per SIMD (LDS holds four tiles per compute unit, and 128 registers just hold
 // the cubic stencils); the traffic alone would take 134 us each way at 512^3.
 // Measured at 512^3 (linear splines), with all levels in this kernel: k_predict
-// 435 us, k_reconstruct 308 us; 16 M points with odd sides (cubic): 126 and 83
+// 438 us, k_reconstruct 308 us; 16 M points with odd sides (cubic): 108 and 83
 // us. With plain rows in LDS, lines along an axis per thread and the coarse
 // levels in a kernel of their own it took 655 and 594, 308 and 287 us.
 #include "hiz_internal.h"
@@ -762,41 +762,55 @@ template <int TZ, int NX> struct CoarsePlan {
     static constexpr int slots(int pass) { return pass == 1 && !T::FLAT ? 2 : 3; }
     uint32_t d0[3], d1[3], d2[3][3];
 
+    // a / b for 0 <= a < 2^12, 0 < b <= 64: (a + 1/2) / b is at least 1 / 128 off a
+    // whole number, far more than the two roundings
+    static __device__ __forceinline__ int small_div(int a, int b)
+    {
+        return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+    }
     static __device__ __forceinline__ uint32_t target(bool md, int order, int l, int pass, int i)
     {
         const int lh = 2 - l;
         const Pass S = make_pass(md, order, pass);
         const int mx = T::FLAT ? 1 : (8 >> lh) + 1, my = (8 >> lh) + 1, mz = (T::KZ >> lh) + 1;
+        // the class this target lies in, and its number there: the same steps for
+        // every lane, so that counts stay scalar, and no integer division (a lane
+        // at a time through the search, with two of them, a workgroup took 3 us
+        // longer per field: 64^3 k_predict 38 us, this way 35; 24 fields of sides
+        // 32..160 168, this way 158)
+        int c = 0, r = -1, first = 0;
         for (uint32_t list = S.classes(); list; list >>= 4) {
-            const int c = list & 7;
-            const int nx = (mx + 1 - (c & 1)) >> 1, ny = (my + 1 - ((c >> 1) & 1)) >> 1,
-                      nz = (mz + 1 - (c >> 2)) >> 1;
-            const int n = nx * ny * nz;
-            if (i >= n) {
-                i -= n;
-                continue;
+            const int k = list & 7;
+            const int n = ((mx + 1 - (k & 1)) >> 1) * ((my + 1 - ((k >> 1) & 1)) >> 1) *
+                          ((mz + 1 - (k >> 2)) >> 1);
+            if (i >= first && i < first + n) {
+                c = k;
+                r = i - first;
             }
-            const int r = i / nz, kx = r / ny;
-            // places on the level's grid
-            const int q[3] = {2 * kx + (c & 1), 2 * (r - kx * ny) + ((c >> 1) & 1),
-                              2 * (i - r * nz) + (c >> 2)};
-            const int u = S.md ? c : S.axis;
-            uint32_t d = (uint32_t)((q[0] * T::LXS + q[1] * T::LP + q[2]) << lh) | (uint32_t)u << 12;
-            const int x = q[0] << lh, y = q[1] << lh, z = q[2] << lh;
-            if (x < 8 && y < 8 && z < T::KZ)
-                d |= (uint32_t)((x * 8 + y) * T::KZ + z) << 21;
-            int bit = 15;
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                if (!((u >> k) & 1))
-                    continue;
-                const int in = q[k] & ((8 >> lh) - 1); // in its block
-                d |= (uint32_t)(in >= 3) << bit | (uint32_t)(in + 3 <= (8 >> lh)) << (bit + 1);
-                bit += 2;
-            }
-            return d;
+            first += n;
         }
-        return 0;
+        if (r < 0)
+            return 0;
+        const int ny = (my + 1 - ((c >> 1) & 1)) >> 1, nz = (mz + 1 - (c >> 2)) >> 1;
+        const int xy = small_div(r, nz), kx = small_div(xy, ny);
+        // places on the level's grid
+        const int q[3] = {2 * kx + (c & 1), 2 * (xy - kx * ny) + ((c >> 1) & 1),
+                          2 * (r - xy * nz) + (c >> 2)};
+        const int u = S.md ? c : S.axis;
+        uint32_t d = (uint32_t)((q[0] * T::LXS + q[1] * T::LP + q[2]) << lh) | (uint32_t)u << 12;
+        const int x = q[0] << lh, y = q[1] << lh, z = q[2] << lh;
+        if (x < 8 && y < 8 && z < T::KZ)
+            d |= (uint32_t)((x * 8 + y) * T::KZ + z) << 21;
+        int bit = 15;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            if (!((u >> k) & 1))
+                continue;
+            const int in = q[k] & ((8 >> lh) - 1); // in its block
+            d |= (uint32_t)(in >= 3) << bit | (uint32_t)(in + 3 <= (8 >> lh)) << (bit + 1);
+            bit += 2;
+        }
+        return d;
     }
     __device__ __forceinline__ void make(const FieldQ &f, int t)
     {
