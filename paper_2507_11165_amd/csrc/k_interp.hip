@@ -1223,7 +1223,13 @@ __global__ __launch_bounds__((Tile<TZ, NX>::NT), 4) void k_predict(const Job *__
             if (cur >= 0)
                 flush(cur);
             cur = ji;
-            skip = (uni32(J.st->flags) & (ST_CONST | ST_NONFINITE)) != 0;
+            // The waves have to agree, or their barriers pair up wrongly from
+            // here on, into the next field's tiles. With a relative bound the
+            // flags are final; with an absolute one this launch sets them while
+            // other waves would read them, so the field is walked to its end
+            // (values that are not finite become outliers of a result that is
+            // then refused).
+            skip = J.mode != 0 && (uni32(J.st->flags) & (ST_CONST | ST_NONFINITE)) != 0;
             f = load_field(J.st, true);
             plan.make(f, t);
         }
