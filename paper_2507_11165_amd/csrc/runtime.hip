@@ -587,11 +587,6 @@ hiz_status resolve_params(hiz_ctx *c, const hiz_params *params, hiz_params &p, i
 // takes none of it (all levels of a tile run in LDS); the published sizes and
 // the limit stay as callers know them.
 uint64_t tile_allowance(uint64_t tz) { return 4 * 81 * (8 * tz + 1) + 512 * tz; }
-uint64_t tile_allowance(const Job &J)
-{
-    return (J.dims[0] / kAnchor) * (J.dims[1] / kAnchor) * (J.dims[2] / kAnchor / J.tz) *
-           tile_allowance(J.tz);
-}
 
 // Geometry and parameters of one field to compress; device pointers are
 // filled in by the caller once the workspace is laid out.
@@ -1409,6 +1404,26 @@ hiz_status resolve_scratch(int device, uint8_t **out)
     return HIZ_OK;
 }
 
+// What the limit of the allocation-free call counts for a field: its sections, a
+// result block and the allowance, for tiles of the depth asked for, or of two
+// blocks along z (one where the field has one). The tiles the launches really use
+// follow the launch table and take no more; the limit does not move with them.
+uint64_t noalloc_need(const Job &job, uint32_t tile_z)
+{
+    Job J = job;
+    const uint64_t tz = tile_z ? tile_z : std::min<uint64_t>(2, J.nb[2]);
+    J.n_tiles = (uint64_t)J.nb[0] * J.nb[1] * cdiv(J.nb[2], tz);
+    Arena A;
+    A.take(sizeof(Job));
+    A.take(sizeof(Counters));
+    A.take(kResultBytes);
+    Totals T;
+    Sections o;
+    take_sections(A, J, false, T, o);
+    return A.off + (J.dims[0] / kAnchor) * (J.dims[1] / kAnchor) * (J.dims[2] / kAnchor / tz) *
+                       tile_allowance(tz);
+}
+
 // One compression through the scratch array: the same plan, layout and launch
 // sequence as hiz_compress, with no device, pinned or heap allocation (the
 // Job table goes up from the pinned block the context allocated at creation,
@@ -1437,14 +1452,13 @@ hiz_status compress_noalloc(hiz_ctx *c, const float *d_field, const uint64_t dim
     Arena A;
     const uint64_t o_jobs = A.take(sizeof(Job));
     const uint64_t o_cnt = A.take(sizeof(Counters));
-    A.take(kResultBytes); // not used: the limit below stays where it was
     Totals T;
     Sections o;
     take_sections(A, J, false, T, o);
     kind_ranges(&J, 1, T);
     if (!totals_fit(T))
         return fail(c, HIZ_ERR_ARG, "field too large for one launch");
-    const uint64_t need = A.off + tile_allowance(J);
+    const uint64_t need = std::max(A.off, noalloc_need(J, p.tile_z));
     if (need > kScratchBytes)
         return fail(c, HIZ_ERR_ARG,
                     "field needs %llu bytes of workspace; the allocation-free call holds at most "
