@@ -225,7 +225,7 @@ hiz_status ctx_decompress_submit_hdrs(hiz_ctx *c, int n, const void *const *d_in
                                       const uint8_t *h_hdrs);
 int reconstruct_blocks_per_cu(int kind);
 // Bitwise-redundancy stages, reordering and outliers (k_lc.hip).
-void launch_reorder(const Job *d_jobs, int njobs, uint64_t max_n, bool inverse, hipStream_t s);
+void launch_reorder(const Job *d_jobs, int njobs, uint64_t max_pieces, bool inverse, hipStream_t s);
 void launch_outliers(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, hipStream_t s);
 void launch_lc_encode(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, hipStream_t s);
 void launch_lc_decode(const Job *d_jobs, int njobs, uint64_t total, Counters *cnt, hipStream_t s);

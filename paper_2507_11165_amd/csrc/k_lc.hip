@@ -1118,11 +1118,13 @@ __global__ __launch_bounds__(256) void k_reorder(const Job *__restrict__ jobs, i
     }
 }
 
-void launch_reorder(const Job *d_jobs, int njobs, uint64_t max_n, bool inverse, hipStream_t s)
+// max_pieces: the most pieces of 16 codes of a row that a field has (rows of fewer
+// codes are one each).
+void launch_reorder(const Job *d_jobs, int njobs, uint64_t max_pieces, bool inverse, hipStream_t s)
 {
-    if (njobs == 0 || max_n == 0)
+    if (njobs == 0 || max_pieces == 0)
         return;
-    uint64_t g = cdiv(cdiv(max_n, 16), 256);
+    uint64_t g = cdiv(max_pieces, 256);
     if (g > 16384)
         g = 16384;
     if (inverse)

@@ -736,7 +736,7 @@ struct Totals {
     uint32_t max_chunk = 0;    // longest Huffman chunk
     bool eps = false;          // some field's relative bound is formed by a launch of its own
     uint64_t lc = 0, ou = 0;   // stage chunks, outlier units
-    uint64_t max_n = 0;        // largest field (reordering launch)
+    uint64_t max_pieces = 0;   // most pieces of 16 codes of a row (reordering launch)
     bool reorder = false;      // some field's codes are reordered
     uint64_t max_clear = 0;    // longest look-back array any field clears at the start
     // per tile kind (jobs ordered by kind): jobs [jlo, jhi) with tiles [tlo, thi)
@@ -776,7 +776,7 @@ void take_sections(Arena &A, Job &J, bool decompress, Totals &T, Sections &o)
     J.ou_begin = T.ou;
     T.lc += J.n_lc;
     T.ou += J.n_ou;
-    T.max_n = std::max(T.max_n, J.N);
+    T.max_pieces = std::max(T.max_pieces, J.N / J.dims[2] * cdiv(J.dims[2], 16));
     T.reorder = T.reorder || J.reorder;
     T.max_clear = std::max(T.max_clear, std::max(J.n_lc, J.n_ou));
     if (decompress) {
@@ -942,7 +942,7 @@ void enqueue_compress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hipS
     }
     if (T.reorder) {
         Scope sc(c, s, "reorder", prof, true);
-        launch_reorder(L.d_jobs, nj, T.max_n, false, s);
+        launch_reorder(L.d_jobs, nj, T.max_pieces, false, s);
     }
     {
         Scope sc(c, s, "codebook", prof, true);
@@ -987,7 +987,7 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
     }
     if (T.reorder) {
         Scope sc(c, s, "unreorder", prof, true);
-        launch_reorder(L.d_jobs, nj, T.max_n, true, s);
+        launch_reorder(L.d_jobs, nj, T.max_pieces, true, s);
     }
     if (T.out) {
         Scope sc(c, s, "scatter", prof, true);
