@@ -207,7 +207,8 @@ void launch_dec_tables(const Job *d_jobs, int njobs, uint64_t max_blocks, hipStr
 // unit) while the units fit the compute units, else 2 * kDecSub.
 constexpr int kDecSub = 256;
 __host__ __device__ inline uint64_t dec_subblocks(uint64_t chunks) { return 2 * cdiv(chunks, 2 * kDecSub); }
-void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, int cus, hipStream_t s);
+void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, uint64_t outliers,
+                   bool reordered, int cus, hipStream_t s);
 void launch_scatter(const Job *d_jobs, int njobs, uint64_t total, hipStream_t s);
 void launch_reconstruct(const Job *d_jobs, int njobs, uint64_t lo, uint64_t hi, int kind, int grid,
                         hipStream_t s);

@@ -1579,18 +1579,35 @@ __global__ __launch_bounds__(NT) void k_decode_split(const Job *__restrict__ job
         atomicAdd((unsigned long long *)&st->zeros_seen, (unsigned long long)zeros);
 }
 
-// total: the call's sub-blocks of kDecSub chunks; longest: its longest chunk.
-void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, int cus, hipStream_t s)
+// total: the call's sub-blocks of kDecSub chunks; longest: its longest chunk;
+// outliers: its outliers; reordered: some field's codes are reordered.
+void launch_decode(const Job *d_jobs, int njobs, uint64_t total, uint32_t longest, uint64_t outliers,
+                   bool reordered, int cus, hipStream_t s)
 {
     if (total == 0)
         return;
     // Several lanes per chunk, the fewer the more chunks there are: the work
     // they add (reading parts twice, ahead of their start) only pays while the
-    // chip has idle lanes. Measured decode times, us, with 64 / 32 / 16 lanes and
-    // one lane per chunk: 1 sub-block (64^3) 28 / 36 / 65 / 179; 8 sub-blocks 24 /
-    // 32 / 49 / 156; 25: 57 / 32 / 49 / 132; 62: 155 / 80 / 66 / 180; 250: 450 / 207 /
-    // 195 / 200; 512 (512^3): 900 / 420 / 420 / 201.
-    if (longest <= (uint32_t)kSplitMax && total <= (uint64_t)cus) {
+    // chip has idle lanes: up to three sub-blocks on four compute units, or, where one
+    // lane per chunk is slow itself, one on each: with an outlier or more per chunk
+    // (every lane then adds to the field's count of them, one after the other) and
+    // for reordered codes. Decode times, us, with 64 / 32 / 16 lanes and one lane
+    // per chunk of 1024, on 256 compute units:
+    //  sub-blocks  turbulence, 1e-3   white noise (7.4     k^-3, 1e-2           turbulence, 1e-4
+    //              (5 bits a code)    bits, all alike)     (3 bits)             (10 to 20 % outliers)
+    //    2         24 /  35 /  63, 199  43 /  57 / 105, 198  21 / 30 /  49, 131   28 /  32 /  57, 161
+    //    8         27 /  37 /  69, 226  43 /  60 / 113, 209  27 / 33 /  56, 138   46 /  54 /  90, 185
+    //   16         40 /  33 /  65, 210  81 /  66 / 116, 230  36 / 31 /  56, 145   89 /  72 / 104, 211
+    //   32         75 /  39 /  63, 191 145 /  69 / 120, 233  60 / 31 /  43, 112  182 / 105 / 115, 261
+    //   64        135 /  68 /  62, 173 264 / 148 / 121, 239 105 / 52 /  44, 112  348 / 212 / 165, 355
+    //  128          - / 138 / 123, 202   - / 245 / 201, 243   - /102 /  88, 116    - / 355 / 256, 545
+    //  192          - / 200 / 186, 204   - / 358 / 291, 256   - /173 / 140, 122    - / 390 / 335, 626
+    //  224          - /   - / 247, 214   - /   - / 370, 248   - /  - / 187, 125    - /   - / 291, 533
+    //  256          - /   - / 248, 208   - /   - / 380, 258   - /  - / 227, 122    - /   - / 335, 553
+    // Reordered, 256: turbulence 204, 400; k^-3 234, 140; 128: 116, 412; 133, 142.
+    const bool slow = reordered || outliers >= total * (uint64_t)kDecSub;
+    const uint64_t most = slow ? (uint64_t)cus : (uint64_t)cus * 3 / 4;
+    if (longest <= (uint32_t)kSplitMax && total <= most) {
         if (total <= (uint64_t)cus / 16)
             hipLaunchKernelGGL((k_decode_split<64, 256>), dim3((uint32_t)(total * 64)), dim3(256), 0, s,
                                d_jobs, njobs);

@@ -983,7 +983,7 @@ void enqueue_decompress(hiz_ctx *c, const Layout &L, int nj, const Totals &T, hi
     }
     if (T.dblk) {
         Scope sc(c, s, "decode", prof, true);
-        launch_decode(L.d_jobs, nj, T.dblk, T.max_chunk, c->cus, s);
+        launch_decode(L.d_jobs, nj, T.dblk, T.max_chunk, T.out, T.reorder, c->cus, s);
     }
     if (T.reorder) {
         Scope sc(c, s, "unreorder", prof, true);
