@@ -70,7 +70,7 @@ typedef struct {
      * 0 = the library's size-keyed default. Recorded in the stream. */
     uint32_t chunk;
     /* Cells along z per GPU tile (1, 2 or 4); 0 = default. Does not change the
-     * output. */
+     * output. Fields of one x plane (dims[0] = 1) always take 4. */
     uint32_t tile_z;
     /* Lossless pipeline (Sec. 5.2.3): HIZ_PIPE_HUFFMAN (default) Huffman
      * coding of the codes; HIZ_PIPE_TP the throughput mode, the stages

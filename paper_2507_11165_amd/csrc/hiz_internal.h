@@ -270,11 +270,6 @@ __device__ __forceinline__ uint64_t uni64(uint64_t u)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u);
     return ((uint64_t)hi << 32) | lo;
 }
-__device__ __forceinline__ float4 gload_f4(HIZ_GLOBAL const float *p)
-{
-    const hiz_f4v v = *(HIZ_GLOBAL const hiz_f4v *)p;
-    return make_float4(v.x, v.y, v.z, v.w);
-}
 __device__ __forceinline__ uint4 gload_u4(HIZ_GLOBAL const uint8_t *p)
 {
     const hiz_u4v v = *(HIZ_GLOBAL const hiz_u4v *)p;
@@ -286,15 +281,6 @@ __device__ __forceinline__ float4 gload_f4_nt(HIZ_GLOBAL const float *p)
 {
     const hiz_f4v v = __builtin_nontemporal_load((HIZ_GLOBAL const hiz_f4v *)p);
     return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void gstore_f4(HIZ_GLOBAL float *p, const float4 &v)
-{
-    hiz_f4v w;
-    w.x = v.x;
-    w.y = v.y;
-    w.z = v.z;
-    w.w = v.w;
-    *(HIZ_GLOBAL hiz_f4v *)p = w;
 }
 __device__ __forceinline__ void gstore_u4(HIZ_GLOBAL uint8_t *p, const uint4 &v)
 {

@@ -29,8 +29,12 @@
 // faces are read through the same L2. The code histogram is kept in LDS for a
 // tile, in registers across the tiles of a field.
 // What bounds it: instruction issue and LDS latency of the levels, at four waves
-// per SIMD (LDS holds four tiles per compute unit, and 128 registers just hold
-// the cubic stencils); the traffic alone would take 134 us each way at 512^3.
+// per SIMD (LDS holds four tiles per compute unit); the traffic alone would take
+// 134 us each way at 512^3. The 128 registers that four waves leave hold all that
+// k_reconstruct and the flat tiles need. k_predict spills: 41 to 44 registers, 56 to
+// 68 bytes of scratch per lane, by tile depth. At 512^3 that is 113 of its 257 MiB
+// written and 119 of its 693 MiB read; with three waves per SIMD it spills nothing
+// and takes 467 us instead of 432.
 // Measured at 512^3 (linear splines), with all levels in this kernel: k_predict
 // 438 us, k_reconstruct 308 us; 16 M points with odd sides (cubic): 108 and 83
 // us. With plain rows in LDS, lines along an axis per thread and the coarse
@@ -62,7 +66,6 @@ template <int TZ, int NX> struct Tile {
     static constexpr int NV = face(4);
     static constexpr int OX = FLAT ? 1 : 8;          // owned lattice points along x
     static constexpr int LXS = 9 * LP;               // lattice words from one x to the next
-    static constexpr int OR = FLAT ? 2 : 4;          // rows a thread owns
     static constexpr int NT = (FLAT ? 8 : 64) * NQ;  // threads: one per owned row group and quad
     static constexpr int NW = NT / 64;
     // rows on the far x and y faces: 17 of even x and y (9 along y at x = 16,
@@ -70,7 +73,6 @@ template <int TZ, int NX> struct Tile {
     static constexpr int NE = (FLAT ? 1 : 33) * NQ;
     // rows of the far z face, those holding targets of the stride-1 level first
     static constexpr int NR = SX * kSide;
-    static constexpr int FT = FLAT ? 8 : 208;
     static constexpr int IF = (NR + NT - 1) / NT;
     static_assert(NT >= 64 && NT % 64 == 0 && NE <= NT, "one face-row quad per thread");
     // word of place (x, y, z) in class c; of far-face place (x, y) in class 1, 2 or 3
@@ -750,9 +752,10 @@ __device__ __forceinline__ void coarse_value(float *__restrict__ v, uint8_t *__r
 }
 
 // Which targets a thread takes in each pass of the three levels depends on the
-// field's configuration alone, so each is worked out once per field and kept in
-// a register: targets i = t, t + NT, ... of the pass's classes one after the
-// other, as a tile with all its points has them. Bits 0..11: the target's lattice
+// field's configuration alone, so each is worked out once per field by every
+// workgroup and kept across its tiles (15 words per thread; k_predict has no
+// registers left for all of them): targets i = t, t + NT, ... of the pass's classes
+// one after the other, as a tile with all its points has them. Bits 0..11: the target's lattice
 // word (0, an anchor: no target); 12..14: its class, or the one axis used; from
 // bit 15 on, per axis used, whether the samples three steps before and after
 // exist; 21..31: where its code goes in compression.
@@ -1154,8 +1157,8 @@ __device__ __forceinline__ void tile_fetch(TileRegs<TZ, NX> &r, const Job &J, co
 // ---------------------------------------------------------------------------
 // Compression: predict + quantize + histogram, persistent over tiles. A tile's
 // values are loaded when its turn comes, the three other workgroups of the
-// compute unit at work meanwhile: held ahead of time in registers (42 of them)
-// they spill what the levels need (512^3: 784 us; at three waves per SIMD 541;
+// compute unit at work meanwhile: held ahead of time in registers (42 more) they
+// make it spill that much more (512^3: 784 us; at three waves per SIMD 541;
 // without 435).
 // ---------------------------------------------------------------------------
 template <int TZ, int NX>

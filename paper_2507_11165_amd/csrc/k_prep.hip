@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void k_init_compress(const Job *__restrict__ h
                 store_bound(st, J.eb);
         }
         // without a sample to measure: the configuration asked for, or the
-        // default one; with one, what a constant field's header records
+        // default one; with one, the tuner's last workgroup stores its choice
         if (t < kLevels) {
             const uint8_t *cf = J.cfg_forced[t];
             if (J.n_tune != 0)
@@ -131,20 +131,6 @@ void launch_init_compress(const Job *h_jobs, Job *d_jobs, int njobs, uint64_t ma
 // whoever needs the bound reduces those. (Atomics on two words of the field
 // instead: 100 x 500 x 500 59 us, this way 29.)
 // ---------------------------------------------------------------------------
-
-__device__ inline uint32_t wave_min_u32(uint32_t v)
-{
-    for (int o = 32; o > 0; o >>= 1)
-        v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-__device__ inline uint32_t wave_max_u32(uint32_t v)
-{
-    for (int o = 32; o > 0; o >>= 1)
-        v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
 __global__ __launch_bounds__(256) void k_minmax(const Job *__restrict__ jobs, int njobs,
                                                 uint64_t total)
 {
